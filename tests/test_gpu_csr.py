@@ -130,3 +130,40 @@ def test_csr_pattern_edge_cases(cf):
     st = cf._lib.coffee_csr_pattern(c2v.data_ptr(), mesh.ncells, 3, mesh.nvert, 1, rp.data_ptr(), small.data_ptr(),
                                     10, C.byref(nnz), ws.data_ptr(), ws.numel(), None)
     assert st == 3 and nnz.value == nnz_expected
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("form,d,p,n", [("helmholtz", 3, 2, 5), ("elasticity", 3, 2, 3), ("mass", 3, 1, 9),
+                                        ("mass", 2, 3, 11), ("elasticity", 2, 2, 7), ("helmholtz", 3, 3, 2)])
+def test_csr_runs_of_scattered_cells(cf, oracle, form, d, p, n, prec):
+    """Cells in random order (runs with more dofs than the LDS matrix has rows are split), counts that leave a
+    partial run, and a pattern that holds more entries than the assembled cells fill."""
+    import torch
+    from gpu_util import TOL, to_dev
+    rng = np.random.default_rng(5 + n)
+    mesh = I.make_mesh(d, n, 0.12, rng)
+    if p == 3:  # every cell its own dofs, then shared at random: any map is a valid space for the scatter
+        nd = mesh.ncells * 3
+        nl = 10 if d == 2 else 20
+        c2d = np.stack([rng.permutation(nd)[:nl] for _ in range(mesh.ncells)]).astype(np.int32)
+    else:
+        c2d, nd = _space(mesh, p)
+    order = rng.permutation(mesh.ncells)
+    cells, c2d = np.ascontiguousarray(mesh.cells[order]), np.ascontiguousarray(c2d[order])
+    cst = [1.5, 0.5] if form == "elasticity" else []
+    nc = d if form == "elasticity" else 1
+    coords, c2v, _ = to_dev(I.Mesh(d, n, mesh.coords, cells), [])
+    dofs = torch.as_tensor(c2d, device=coords.device)
+    row_ptr, col_idx = cf.coffee_csr_pattern(dofs, nd, nc)
+    rp, ci = row_ptr.cpu().numpy(), col_idx.cpu().numpy()
+    for count in (1, 7, mesh.ncells - 1, mesh.ncells):
+        sub = I.Mesh(d, n, mesh.coords, np.ascontiguousarray(cells[:count]))
+        A = oracle.assemble(form, sub, p, constants=cst)
+        got = cf.coffee_assemble_csr(form, d, p, coords, c2v[:count].contiguous(), row_ptr, col_idx, nd,
+                                     cell_to_dof=dofs[:count].contiguous(), constants=cst, precision=prec).cpu().numpy()
+        g = np.concatenate([c2d[:count].astype(np.int64) * nc + c for c in range(nc)], axis=1)
+        keys = np.repeat(np.arange(nd * nc), np.diff(rp)) * (nd * nc) + ci
+        ref = np.zeros(len(ci))
+        np.add.at(ref, np.searchsorted(keys, (g[:, :, None] * (nd * nc) + g[:, None, :]).ravel()), A.ravel())
+        # entries are sums of at most a few dozen tensor values of that size
+        assert np.abs(got - ref).max() <= 10 * TOL[prec] * np.abs(A).max(), count
