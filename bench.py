@@ -280,13 +280,17 @@ def measure_forward(ctx, w, prec, sample_n=300, seed=3, tag=None):
 
 
 def adjoint_flops_per_cell(w):
-    """Multiply-adds x 2 of the contraction the elasticity adjoint implements:
-    V_k = R_k u_c2, then lam_c1 . V_k, for every entry k and block (c1, c2)."""
+    """Multiply-adds x 2 of the node form the elasticity adjoint implements:
+    physical gradients of lam and u at the nv nodes of degree p - 1, the pair
+    products and their coefficient weights, the weighted gradients W and T."""
     if w.form != "elasticity":
         return None
-    d, ns = w.mesh.d, n_scalar(w.mesh.d, w.degree)
-    nf = n_scalar(d, 1) if w.fields else 1
-    return 2.0 * nf * d * d * d * (ns * ns + d * ns)
+    d, p = w.mesh.d, w.degree
+    nv = 1 if p == 1 else d + 1
+    nf = d + 1
+    pairs = nv * (nv + 1) // 2
+    grads = 2 * d * nv * (2 * d + d * d)
+    return 2.0 * (grads + pairs * (2 * d * d + 4 * nf) + 2 * nv * (nv * (d * (d + 1) // 2 + 1) + d * d * (d + 1)))
 
 
 def measure_adjoint(ctx, w, tag):

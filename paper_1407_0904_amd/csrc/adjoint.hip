@@ -258,201 +258,261 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
     }
 }
 
-// Elasticity: the contraction T = lam_c1^T R_k u_c2 factored as
-// V_k = R_k u_c2 (shared by the NC test components c1) and T = lam_c1 . V_k,
-// consumed entry by entry: for k = (r, alpha, beta) and every block (c1, c2)
-// the transpose of G's entry
-//     G = |det J| (mu_r (delta_c1c2 (K K^T)_ab + K[a][c2] K[b][c1]) + lambda_r K[a][c1] K[b][c2])
-// (the same arithmetic as reverse_G in linear.hpp, per entry instead of per
-// block). lam_e stays in registers, u_e rows are re-read per dof r (L1), R is
-// read through the scalar path (its addresses are the same in every lane; from
-// LDS each wave-wide read of one value would cost as much LDS bandwidth as a
-// read of 64 different values). Per cell: NF D^2 NC (NS^2 +
-// NC NS) multiply-adds for the values (14k for P2 tetrahedra, against 32k for
-// the per-block contraction), and the dof r's coefficient bars are added to
-// the global gradients as soon as its loop ends.
-template <int D, typename T>
-__device__ inline T sel_rt(const T* x, int n, int r) {
-    T v = T(0);
-    for (int j = 0; j < n; ++j) v += (r == j ? T(1) : T(0)) * x[j];
-    return v;
+// Elasticity, degrees 1 and 2. The gradients of lam and u on a cell are
+// polynomials of degree P - 1, fixed by their values H_k at the NV nodes of
+// that degree (one node, or the vertices), and with
+//     c_rkl = sum_q W_q psi_r N_k N_l   (psi_r: coefficient basis, N_k: degree P - 1 basis)
+// the quadrature sum is exactly
+//     S = |det J| sum_kl (sum_r c_rkl mu_r) 2 eps(Hlam_k):eps(Hu_l) + (sum_r c_rkl lambda_r) tr Hlam_k tr Hu_l.
+// Each H_k takes a few differences of dofs (grad_nodes), so a cell costs about
+// 1,000 multiply-adds for P2 tetrahedra, gradients included, where
+// contracting lam and u with the reference tensors of all pairs of basis
+// functions took 14,000 (663,552 cells: 665 us for that kernel, 190 for this).
+// With Wu_k = sum_l (mu_kl (Hu_l + Hu_l^T) + lambda_kl tr Hu_l I), symmetric,
+// and Wlam_k likewise: S = |det J| sum_k Hlam_k : Wu_k, and since every H is
+// (reference gradient) K, the derivative in J is (S I - T) K^T,
+//     T = |det J| sum_k (Hlam_k^T Wu_k + Hu_k^T Wlam_k).
+// What is left is the read of lam and u, 480 bytes per cell: component by
+// component through LDS (coalesced 8-byte reads, the next component in flight
+// while the current one is used), into rows of odd length per cell.
+
+// Reference gradient of one component with dofs v at the nodes of degree P - 1.
+template <int D>
+constexpr int edge_dof(int i, int j) {
+    const int lo = i < j ? i : j, hi = i < j ? j : i;
+    if (D == 2) return 3 + (lo == 1 ? 0 : (hi == 2 ? 1 : 2));
+    return 4 + (lo == 2 ? 0 : lo == 1 ? (hi == 3 ? 1 : 2) : (hi == 3 ? 3 : (hi == 2 ? 4 : 5)));
 }
 
+template <int D, int P>
+__device__ inline void grad_nodes(const double (&v)[nsc(D, P)], double (&g)[P == 1 ? 1 : D + 1][D]) {
+    static_assert(P == 1 || P == 2, "degree");
+    if constexpr (P == 1) {
+#pragma unroll
+        for (int a = 0; a < D; ++a) g[0][a] = v[a + 1] - v[0];
+    } else {
+        // d/d lambda_i at vertex k: 3 v_k for i = k, else 4 v_edge(k,i) - v_i
+#pragma unroll
+        for (int k = 0; k <= D; ++k) {
+            double b[D + 1];
+#pragma unroll
+            for (int i = 0; i <= D; ++i) b[i] = i == k ? 3.0 * v[k] : 4.0 * v[edge_dof<D>(k, i)] - v[i];
+#pragma unroll
+            for (int a = 0; a < D; ++a) g[k][a] = b[a + 1] - b[0];
+        }
+    }
+}
+
+// The H of P2 tetrahedra (144 registers) and what is formed from them need one
+// wave per SIMD: at two, 255 registers spilled (352 us against 190).
 template <int D, int P, int FD>
-__global__ __launch_bounds__(256, 2) void k_adjoint_elast(AdjArgs A) {
-    constexpr int NS = nsc(D, P), NN = NS * NS, NC = D, N = NC * NS;
-    constexpr int NF = nfield(D, FD), KR = NF * D * D;
-    (void)KR;
-    // per-wave combining of the gradient scatter-adds (vertex coordinates,
-    // then the two fields' dofs)
+__global__ __launch_bounds__(256, (D == 3 && P == 2) ? 1 : 2) void k_adjoint_elast(AdjArgs A) {
+    constexpr int NS = nsc(D, P), N = D * NS, NV = P == 1 ? 1 : D + 1, NF = nfield(D, FD), ROW = NS | 1;
+    static_assert(FD == 1, "P1 coefficients");
+    // per-wave combining of the gradient scatter-adds (vertex coordinates and
+    // the two fields' dofs); the dof staging shares the memory of the values
     constexpr int TS = 256;
+    static_assert(64 * ROW <= TS * D, "staging");
     __shared__ unsigned long long ckx[4][TS], ckf[4][2][TS];
     __shared__ double cvx[4][TS * D], cvf[4][2][TS];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // wave-uniform loop: every lane takes part in the tables' clear and flush
+    double* stage = cvx[wave];
+    const bool det = A.det_x != nullptr;  // same in every lane, as the next
+    const bool shared_keys = A.L.f0.map == A.L.c2v && A.L.f1.map == A.L.c2v;  // the fields' dofs are the vertices
+    // wave-uniform loop: every lane takes part in the staging, clear and flush
     for (int64_t base = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) - lane; base < A.L.ncells;
          base += (int64_t)gridDim.x * blockDim.x) {
         const bool valid = base + lane < A.L.ncells;
-        const int64_t cell = valid ? base + lane : A.L.ncells - 1;
-        const bool det = A.det_x != nullptr;  // same in every lane
+        const int last = A.L.ncells - base < 64 ? (int)(A.L.ncells - base) - 1 : 63;
+        const int64_t cell = base + (lane < last ? lane : last);
+        const double* src[2] = {A.lam + base * N, A.u + base * N};
+        double pre[NS];  // component c of the wave's cells: flat entry 64 i + lane
+        auto fetch = [&](const double* x, int c) {
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                const int t = 64 * i + lane, e = t / NS, a = t - e * NS;
+                pre[i] = gload(x + (e < last ? e : last) * N + c * NS + a);
+            }
+        };
+        CellIdx<F_ELAST, D, FD> ix;
+        CellRaw<F_ELAST, D, FD> raw;
+        load_idx<F_ELAST, D, FD>(A.L, cell, ix);
+        fetch(src[0], 0);
+        load_raw<F_ELAST, D, FD>(A.L, cell, ix, raw);
+        CellData<F_ELAST, D, FD, double> cd;
+        cell_from_raw<F_ELAST, D, FD>(raw, cd);
+        const auto& K = cd.g.K;
+        const double ad = cd.g.adet;
+        double H[2][NV][D][D];  // physical gradients of lam, u at the nodes
+        wave_sync();
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    const int t = 64 * i + lane, e = t / NS;
+                    stage[e * ROW + t - e * NS] = pre[i];
+                }
+                if (c + 1 < D) fetch(src[f], c + 1);
+                else if (f == 0) fetch(src[1], 0);
+                wave_sync();
+                double v[NS], g[NV][D];
+#pragma unroll
+                for (int i = 0; i < NS; ++i) v[i] = stage[lane * ROW + i];
+                wave_sync();
+                grad_nodes<D, P>(v, g);
+#pragma unroll
+                for (int k = 0; k < NV; ++k)
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        double x = 0.0;
+#pragma unroll
+                        for (int a = 0; a < D; ++a) x += g[k][a] * K[a][j];
+                        H[f][k][c][j] = x;
+                    }
+            }
         if (!det) {
             combine_clear<D, TS>(ckx[wave], cvx[wave], lane);
             combine_clear<1, TS>(ckf[wave][0], cvf[wave][0], lane);
             combine_clear<1, TS>(ckf[wave][1], cvf[wave][1], lane);
             wave_sync();
         }
-        CellIdx<F_ELAST, D, FD> ix;
-        CellRaw<F_ELAST, D, FD> raw;
-        load_idx<F_ELAST, D, FD>(A.L, cell, ix);
-        load_raw<F_ELAST, D, FD>(A.L, cell, ix, raw);
-        CellData<F_ELAST, D, FD, double> cd;
-        cell_from_raw<F_ELAST, D, FD>(raw, cd);
-        const auto& K = cd.g.K;
-        const double ad = cd.g.adet;
-        const double* lam_e = A.lam + cell * N;
-        const double* u_e = A.u + cell * N;
-        double lam[N];
+        double tr[2][NV];
 #pragma unroll
-        for (int i = 0; i < N; ++i) lam[i] = lam_e[i];
-        double S = 0.0, Kbar[D][D];
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                tr[f][k] = 0.0;
+#pragma unroll
+                for (int i = 0; i < D; ++i) tr[f][k] += H[f][k][i][i];
+            }
+        // coefficient weights of the node pairs and, with the pair products
+        // eps:eps and tr tr, the bars of the coefficient dofs
+        double mw[NV][NV], lw[NV][NV], mub[NF], lmb[NF];
+#pragma unroll
+        for (int r = 0; r < NF; ++r) mub[r] = lmb[r] = 0.0;
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+#pragma unroll
+            for (int l = k; l < NV; ++l) {
+                double pm = 0.0, pl = tr[0][k] * tr[1][l];
+#pragma unroll
+                for (int i = 0; i < D; ++i)
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        pm += H[0][k][i][j] * (H[1][l][i][j] + H[1][l][j][i]);
+                        if (l != k) pm += H[0][l][i][j] * (H[1][k][i][j] + H[1][k][j][i]);
+                    }
+                if (l != k) pl += tr[0][l] * tr[1][k];
+                double m = 0.0, q = 0.0;
+#pragma unroll
+                for (int r = 0; r < NF; ++r) {
+                    const double c = cload(A.R + (r * NV + k) * NV + l);
+                    m += c * cd.f0[r];
+                    q += c * cd.f1[r];
+                    mub[r] += c * pm;
+                    lmb[r] += c * pl;
+                }
+                mw[k][l] = mw[l][k] = m;
+                lw[k][l] = lw[l][k] = q;
+            }
+        // S and T
+        double S = 0.0, T[D][D];
 #pragma unroll
         for (int i = 0; i < D; ++i)
 #pragma unroll
-            for (int j = 0; j < D; ++j) Kbar[i][j] = 0.0;
-#pragma unroll 1
-        for (int r = 0; r < NF; ++r) {
-            const double mu = FD > 0 ? sel_rt<D>(cd.f0, NF, r) : A.L.c0;
-            const double lm = FD > 0 ? sel_rt<D>(cd.f1, NF, r) : A.L.c1;
-            double mub = 0.0, lmb = 0.0;
+            for (int j = 0; j < D; ++j) T[i][j] = 0.0;
 #pragma unroll
-            for (int c2 = 0; c2 < NC; ++c2) {
-                double u[NS];
+        for (int k = 0; k < NV; ++k)
 #pragma unroll
-                for (int b = 0; b < NS; ++b) u[b] = u_e[c2 * NS + b];
-                // (alpha, beta) in a rolled loop; the rows K[alpha][.] and
-                // K[beta][.] are picked arithmetically and the Kbar updates of
-                // the two rows collected in xa, xb and added back the same way
-#pragma unroll 1
-                for (int ab = 0; ab < D * D; ++ab) {
-                    const int al = ab / D, be = ab - (ab / D) * D;
-                    double Ka[D], Kb[D];
+            for (int f = 0; f < 2; ++f) {
+                // W of the other field at node k
+                double Wk[D][D], dil = 0.0;
 #pragma unroll
-                    for (int i = 0; i < D; ++i) {
-                        double x = 0.0, y = 0.0;
+                for (int l = 0; l < NV; ++l) dil += lw[k][l] * tr[1 - f][l];
 #pragma unroll
-                        for (int row = 0; row < D; ++row) {
-                            x += (row == al ? 1.0 : 0.0) * K[row][i];
-                            y += (row == be ? 1.0 : 0.0) * K[row][i];
-                        }
-                        Ka[i] = x;
-                        Kb[i] = y;
-                    }
-                    const double* Rk = A.R + (r * D * D + ab) * NN;
-                    double V[NS];
+                for (int i = 0; i < D; ++i)
 #pragma unroll
-                    for (int a = 0; a < NS; ++a) {
-                        double v = 0.0;
+                    for (int j = i; j < D; ++j) {
+                        double x = i == j ? dil : 0.0;
 #pragma unroll
-                        for (int b = 0; b < NS; ++b) v += cload(Rk + a * NS + b) * u[b];
-                        V[a] = v;
-                    }
-                    double kk = 0.0;  // (K K^T)_{alpha beta}
-#pragma unroll
-                    for (int i = 0; i < D; ++i) kk += Ka[i] * Kb[i];
-                    double xa[D], xb[D];
-#pragma unroll
-                    for (int i = 0; i < D; ++i) xa[i] = xb[i] = 0.0;
-#pragma unroll
-                    for (int c1 = 0; c1 < NC; ++c1) {
-                        double g = 0.0;
-#pragma unroll
-                        for (int a = 0; a < NS; ++a) g += lam[c1 * NS + a] * V[a];
-                        const double gb = ad * g;
-                        mub += gb * ((c1 == c2 ? kk : 0.0) + Ka[c2] * Kb[c1]);
-                        lmb += gb * Ka[c1] * Kb[c2];
-                        const double gm = gb * mu, gl = gb * lm;
-                        if (c1 == c2) {
-#pragma unroll
-                            for (int i = 0; i < D; ++i) {
-                                xa[i] += gm * Kb[i];
-                                xb[i] += gm * Ka[i];
-                            }
-                        }
-                        xa[c2] += gm * Kb[c1];
-                        xb[c1] += gm * Ka[c2];
-                        xa[c1] += gl * Kb[c2];
-                        xb[c2] += gl * Ka[c1];
+                        for (int l = 0; l < NV; ++l) x += mw[k][l] * (H[1 - f][l][i][j] + H[1 - f][l][j][i]);
+                        Wk[i][j] = Wk[j][i] = x;
                     }
 #pragma unroll
-                    for (int row = 0; row < D; ++row) {
-                        const double wa = row == al ? 1.0 : 0.0, wb = row == be ? 1.0 : 0.0;
+                for (int c = 0; c < D; ++c)
 #pragma unroll
-                        for (int i = 0; i < D; ++i) Kbar[row][i] += wa * xa[i] + wb * xb[i];
+                    for (int j = 0; j < D; ++j) {
+                        if (f == 0) S += H[0][k][c][j] * Wk[c][j];
+#pragma unroll
+                        for (int i = 0; i < D; ++i) T[i][j] += H[f][k][c][i] * Wk[c][j];
                     }
-                }
             }
-            S += mu * mub + lm * lmb;
-            if constexpr (FD > 0) {
-                if (det) {
-                    if (valid) {
-                        A.det_f0[cell * NF + r] = A.seed * mub;
-                        A.det_f1[cell * NF + r] = A.seed * lmb;
-                    }
-                } else if (A.grad_f0 && valid) {
-                    const int64_t i0 = A.L.f0.map ? (int64_t)A.L.f0.map[cell * NF + r] : cell * NF + r;
-                    const double x = A.seed * mub;
-                    combine_add<1, TS>(ckf[wave][0], cvf[wave][0], (unsigned long long)i0, &x, A.grad_f0);
-                }
-                if (!det && A.grad_f1 && valid) {
-                    const int64_t i1 = A.L.f1.map ? (int64_t)A.L.f1.map[cell * NF + r] : cell * NF + r;
-                    const double x = A.seed * lmb;
-                    combine_add<1, TS>(ckf[wave][1], cvf[wave][1], (unsigned long long)i1, &x, A.grad_f1);
-                }
-            }
-        }
+        S *= ad;
         if (A.cell_value && valid) A.cell_value[cell] = S;
-        // chain to the coordinates (as in k_adjoint_linear)
-        double Jbar[D][D];
+        // chain to the coordinates: Jbar = (S I - T) K^T, xbar_{j+1} = Jbar[:, j]
+        const double sd = A.seed;
+        double vx[D + 1][D];
 #pragma unroll
-        for (int i = 0; i < D; ++i)
+        for (int i = 0; i < D; ++i) {
+            double x0 = 0.0;
 #pragma unroll
             for (int j = 0; j < D; ++j) {
-                double t = 0.0;
+                double t = S * K[j][i];
 #pragma unroll
-                for (int a = 0; a < D; ++a)
-#pragma unroll
-                    for (int b = 0; b < D; ++b) t += K[a][i] * Kbar[a][b] * K[j][b];
-                Jbar[i][j] = -t + S * K[j][i];
+                for (int a = 0; a < D; ++a) t -= ad * T[i][a] * K[j][a];
+                vx[j + 1][i] = sd * t;
+                x0 -= t;
             }
-        const double sd = A.seed;
-        if (valid) {
-            double vx[D + 1][D];
+            vx[0][i] = sd * x0;
+        }
+        if (valid && det) {
 #pragma unroll
-            for (int i = 0; i < D; ++i) {
-                double x0 = 0.0;
+            for (int v = 0; v <= D; ++v)
 #pragma unroll
-                for (int j = 0; j < D; ++j) {
-                    vx[j + 1][i] = sd * Jbar[i][j];
-                    x0 -= Jbar[i][j];
+                for (int i = 0; i < D; ++i) A.det_x[(cell * (D + 1) + v) * D + i] = vx[v][i];
+#pragma unroll
+            for (int r = 0; r < NF; ++r) {
+                A.det_f0[cell * NF + r] = sd * ad * mub[r];
+                A.det_f1[cell * NF + r] = sd * ad * lmb[r];
+            }
+        } else if (valid && !det) {
+#pragma unroll
+            for (int r = 0; r < NF; ++r) {
+                const double m = sd * ad * mub[r], q = sd * ad * lmb[r];
+                if (shared_keys) {
+                    // vertex r: coordinates and both coefficients in one slot
+                    const int h = combine_slot<TS>(ckx[wave], (unsigned long long)ix.v[r]);
+                    if (h >= 0) {
+#pragma unroll
+                        for (int i = 0; i < D; ++i) atomicAdd(&cvx[wave][h * D + i], vx[r][i]);
+                        atomicAdd(&cvf[wave][0][h], m);
+                        atomicAdd(&cvf[wave][1][h], q);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < D; ++i)
+                            if (A.grad_coords) atomicAdd(A.grad_coords + (int64_t)ix.v[r] * D + i, vx[r][i]);
+                        if (A.grad_f0) atomicAdd(A.grad_f0 + ix.v[r], m);
+                        if (A.grad_f1) atomicAdd(A.grad_f1 + ix.v[r], q);
+                    }
+                } else {
+                    if (A.grad_coords)
+                        combine_add<D, TS>(ckx[wave], cvx[wave], (unsigned long long)ix.v[r], vx[r], A.grad_coords);
+                    const int64_t i0 = A.L.f0.map ? (int64_t)ix.f0[r] : cell * NF + r;
+                    const int64_t i1 = A.L.f1.map ? (int64_t)ix.f1[r] : cell * NF + r;
+                    if (A.grad_f0) combine_add<1, TS>(ckf[wave][0], cvf[wave][0], (unsigned long long)i0, &m, A.grad_f0);
+                    if (A.grad_f1) combine_add<1, TS>(ckf[wave][1], cvf[wave][1], (unsigned long long)i1, &q, A.grad_f1);
                 }
-                vx[0][i] = sd * x0;
-            }
-            if (det) {
-#pragma unroll
-                for (int v = 0; v <= D; ++v)
-#pragma unroll
-                    for (int i = 0; i < D; ++i) A.det_x[(cell * (D + 1) + v) * D + i] = vx[v][i];
-            } else if (A.grad_coords) {
-#pragma unroll
-                for (int v = 0; v <= D; ++v)
-                    combine_add<D, TS>(ckx[wave], cvx[wave], (unsigned long long)ix.v[v], vx[v], A.grad_coords);
             }
         }
         if (!det) {
             wave_sync();
+            const unsigned long long* k0 = shared_keys ? ckx[wave] : ckf[wave][0];
+            const unsigned long long* k1 = shared_keys ? ckx[wave] : ckf[wave][1];
             if (A.grad_coords) combine_flush<D, TS>(ckx[wave], cvx[wave], A.grad_coords, lane);
-            if (A.grad_f0) combine_flush<1, TS>(ckf[wave][0], cvf[wave][0], A.grad_f0, lane);
-            if (A.grad_f1) combine_flush<1, TS>(ckf[wave][1], cvf[wave][1], A.grad_f1, lane);
+            if (A.grad_f0) combine_flush<1, TS>(k0, cvf[wave][0], A.grad_f0, lane);
+            if (A.grad_f1) combine_flush<1, TS>(k1, cvf[wave][1], A.grad_f1, lane);
             wave_sync();
         }
     }
@@ -466,10 +526,11 @@ struct AdjEntry {
     AdjLaunch launch;
 };
 
-// Elasticity uses the factored kernel when its reference tensor fits in LDS.
+// Elasticity at the registered degrees (1 and 2, P1 coefficients) uses the
+// node kernel, whose table AdjArgs::R is c_rkl (node_weights).
 template <int FORM, int D, int P, int FD>
 hipError_t launch_adjoint(const dev::AdjArgs& a, hipStream_t s, int grid) {
-    if constexpr (FORM == dev::F_ELAST && dev::adj_r_in_lds<FORM, D, P, FD>())
+    if constexpr (FORM == dev::F_ELAST)
         hipLaunchKernelGGL((dev::k_adjoint_elast<D, P, FD>), dim3(grid), dim3(256), 0, s, a);
     else
         hipLaunchKernelGGL((dev::k_adjoint_linear<FORM, D, P, FD>), dim3(grid), dim3(256), 0, s, a);
@@ -513,18 +574,37 @@ bool r64_table(int form, int dim, int p, int q, int fd, std::vector<double>& h) 
     return true;
 }
 
-// FP64 reference tensors [KR][NS * NS] (unpacked), built and uploaded on first
-// use; shared by the adjoint kernels and the degree-1 FMA kernels.
-coffee_status reference_table_f64(int dev, int form, int dim, int p, int q, int fd, const double** out) {
+// c_rkl = sum_q W_q psi_r N_k N_l [NF][NV][NV]: coefficient basis of degree
+// fd, nodal basis of degree p - 1.
+static bool node_weights(int dim, int p, int q, int fd, std::vector<double>& h) {
+    Tables nd, fl;
+    if (!nd.init(dim, p - 1, q) || !fl.init(dim, fd, q)) return false;
+    h.assign((size_t)fl.n * nd.n * nd.n, 0.0);
+    for (int r = 0; r < fl.n; ++r)
+        for (int k = 0; k < nd.n; ++k)
+            for (int l = 0; l < nd.n; ++l) {
+                long double s = 0.0L;
+                for (int t = 0; t < nd.nq; ++t)
+                    s += nd.W[t] * fl.phi[(size_t)t * fl.n + r] * nd.phi[(size_t)t * nd.n + k] *
+                         nd.phi[(size_t)t * nd.n + l];
+                h[((size_t)r * nd.n + k) * nd.n + l] = (double)s;
+            }
+    return true;
+}
+
+constexpr int kNodeWeights = 0x100;  // added to the form in the table key
+
+// A device table of g_adj_tables, built by `build` and uploaded on first use.
+template <typename B>
+static coffee_status device_table(const std::tuple<int, int, int, int, int, int>& key, B&& build, const double** out) {
     std::lock_guard<std::mutex> lk(g_adj_mu);
-    auto key = std::make_tuple(dev, form, dim, p, q, fd);
     auto it = g_adj_tables.find(key);
     if (it != g_adj_tables.end()) {
         *out = (const double*)it->second;
         return COFFEE_OK;
     }
     std::vector<double> h;
-    if (!r64_table(form, dim, p, q, fd, h)) return COFFEE_E_INVALID_ARG;
+    if (!build(h)) return COFFEE_E_INVALID_ARG;
     void* d = nullptr;
     if (hipMalloc(&d, h.size() * sizeof(double)) != hipSuccess) return COFFEE_E_NOMEM;
     if (hipMemcpy(d, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess) {
@@ -534,6 +614,13 @@ coffee_status reference_table_f64(int dev, int form, int dim, int p, int q, int 
     g_adj_tables[key] = d;
     *out = (const double*)d;
     return COFFEE_OK;
+}
+
+// FP64 reference tensors [KR][NS * NS] (unpacked), built and uploaded on first
+// use; shared by the adjoint kernels and the degree-1 FMA kernels.
+coffee_status reference_table_f64(int dev, int form, int dim, int p, int q, int fd, const double** out) {
+    return device_table(std::make_tuple(dev, form, dim, p, q, fd),
+                        [&](std::vector<double>& h) { return r64_table(form, dim, p, q, fd, h); }, out);
 }
 
 void free_adjoint_tables() {
@@ -559,7 +646,11 @@ coffee_status adjoint_linear(int form, int cell, int degree, int q, int fd, cons
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return COFFEE_E_HIP;
     const double* R = nullptr;
-    coffee_status st = reference_table_f64(dev, form, cell, degree, q, fd, &R);
+    coffee_status st =
+        form == COFFEE_ELASTICITY
+            ? device_table(std::make_tuple(dev, form + kNodeWeights, cell, degree, q, fd),
+                           [&](std::vector<double>& h) { return node_weights(cell, degree, q, fd, h); }, &R)
+            : reference_table_f64(dev, form, cell, degree, q, fd, &R);
     if (st != COFFEE_OK) return st;
     dev::AdjArgs a;
     std::memset(&a, 0, sizeof a);

@@ -544,6 +544,18 @@ __device__ inline void combine_clear(unsigned long long* keys, double* vals, int
     }
 }
 
+// The slot of a key, inserted if it is new; -1 if the probe limit is reached.
+template <int TS>
+__device__ inline int combine_slot(unsigned long long* keys, unsigned long long key) {
+    unsigned h = (unsigned)((key * 0x9E3779B97F4A7C15ull) >> 40) & (TS - 1);
+    for (int t = 0; t < 32; ++t) {
+        const unsigned long long old = atomicCAS(&keys[h], kEmptyKey, key);
+        if (old == kEmptyKey || old == key) return (int)h;
+        h = (h + 1) & (TS - 1);
+    }
+    return -1;
+}
+
 template <int NV, int TS>
 __device__ inline void combine_add(unsigned long long* keys, double* vals, unsigned long long key, const double* v,
                                    double* global_base) {

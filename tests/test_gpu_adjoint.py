@@ -257,3 +257,45 @@ def test_value_only_reverse_pass(cf):
     torch.cuda.synchronize()
     assert gc is None and gf == []
     assert torch.equal(cv0, cv1)
+
+
+@pytest.mark.parametrize("q", [-1, 1, 2, 16 + 3])
+@pytest.mark.parametrize("d,p", [(2, 1), (2, 2), (3, 1), (3, 2)])
+def test_elasticity_adjoint_ragged_counts_and_maps(cf, oracle, d, p, q):
+    """Counts around the 64-cell wave and the 256-cell workgroup, rules that integrate the form exactly and rules that
+    do not, and the three ways the coefficients reach the kernel: the vertex map itself, another map, cell-major."""
+    import torch
+    from gpu_util import to_dev
+    rng = np.random.default_rng(7 + 10 * d + p)
+    mesh = I.make_mesh(d, 12 if d == 2 else 4, 0.15, rng)
+    mu, lm = rng.uniform(1, 10, (mesh.nvert, 1)), rng.uniform(1, 10, (mesh.nvert, 1))
+    N = d * I.n_scalar_dofs(d, p)
+    lam, u = rng.standard_normal((mesh.ncells, N)), rng.standard_normal((mesh.ncells, N))
+    for count in (1, 63, 64, 65, 257):
+        sub = I.Mesh(d, mesh.n, mesh.coords, np.ascontiguousarray(mesh.cells[:count]))
+        ref = oracle.adjoint("elasticity", sub, p, q if q >= 0 else 2 * p,
+                             fields=[I.Field(v, sub.cells, 1, 1) for v in (mu, lm)], lam=lam[:count], u=u[:count])
+        S, gc, gf = ref[0], ref[1], ref[2]
+        coords, c2v, _ = to_dev(sub, [])
+        other = c2v.clone()
+        for kind in ("vertex", "map", "cellmajor"):
+            if kind == "cellmajor":
+                fs = [cf.DeviceField(torch.as_tensor(v[sub.cells], device=c2v.device).contiguous(), None, 1, 1)
+                      for v in (mu, lm)]
+            else:
+                fs = [cf.DeviceField(torch.as_tensor(v, device=c2v.device), c2v if kind == "vertex" else other, 1, 1)
+                      for v in (mu, lm)]
+            cv = torch.empty(count, dtype=torch.float64, device=c2v.device)
+            hc, hf = cf.coffee_assemble_adjoint(
+                "elasticity", d, p, coords, c2v, coeffs=fs, lam=torch.as_tensor(lam[:count], device=c2v.device),
+                u=torch.as_tensor(u[:count], device=c2v.device), cell_value=cv, quad_degree=q)
+            hf = [g.cpu().numpy() for g in hf]
+            if kind == "cellmajor":
+                for i in range(2):
+                    g = np.zeros((mesh.nvert, 1))
+                    np.add.at(g, sub.cells, hf[i].reshape(count, d + 1, 1))
+                    hf[i] = g
+            assert rel(hc.cpu().numpy(), gc) < 1e-11, (count, kind)
+            for a, b in zip(hf, gf):
+                assert rel(a.reshape(b.shape), b) < 1e-11, (count, kind)
+            assert abs(float(cv.sum()) - float(np.sum(S))) <= 1e-11 * float(cv.abs().sum())
