@@ -276,33 +276,6 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
 // component through LDS (coalesced 8-byte reads, the next component in flight
 // while the current one is used), into rows of odd length per cell.
 
-// Reference gradient of one component with dofs v at the nodes of degree P - 1.
-template <int D>
-constexpr int edge_dof(int i, int j) {
-    const int lo = i < j ? i : j, hi = i < j ? j : i;
-    if (D == 2) return 3 + (lo == 1 ? 0 : (hi == 2 ? 1 : 2));
-    return 4 + (lo == 2 ? 0 : lo == 1 ? (hi == 3 ? 1 : 2) : (hi == 3 ? 3 : (hi == 2 ? 4 : 5)));
-}
-
-template <int D, int P>
-__device__ inline void grad_nodes(const double (&v)[nsc(D, P)], double (&g)[P == 1 ? 1 : D + 1][D]) {
-    static_assert(P == 1 || P == 2, "degree");
-    if constexpr (P == 1) {
-#pragma unroll
-        for (int a = 0; a < D; ++a) g[0][a] = v[a + 1] - v[0];
-    } else {
-        // d/d lambda_i at vertex k: 3 v_k for i = k, else 4 v_edge(k,i) - v_i
-#pragma unroll
-        for (int k = 0; k <= D; ++k) {
-            double b[D + 1];
-#pragma unroll
-            for (int i = 0; i <= D; ++i) b[i] = i == k ? 3.0 * v[k] : 4.0 * v[edge_dof<D>(k, i)] - v[i];
-#pragma unroll
-            for (int a = 0; a < D; ++a) g[k][a] = b[a + 1] - b[0];
-        }
-    }
-}
-
 // The H of P2 tetrahedra (144 registers) and what is formed from them need one
 // wave per SIMD: at two, 255 registers spilled (352 us against 190).
 template <int D, int P, int FD>

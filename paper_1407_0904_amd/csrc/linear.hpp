@@ -128,6 +128,69 @@ struct Geom {
     T adet;
 };
 
+// ---------------------------------------------------------------- gradients at nodes
+// The gradient of a degree-P function on a cell is a polynomial of degree
+// P - 1, fixed by its values at the NV nodes of that degree: one node for
+// P = 1, the vertices for P = 2.
+constexpr int grad_nv(int d, int p) { return p == 1 ? 1 : d + 1; }
+
+// Local dof of the P2 edge (i, j).
+template <int D>
+constexpr int edge_dof(int i, int j) {
+    const int lo = i < j ? i : j, hi = i < j ? j : i;
+    if (D == 2) return 3 + (lo == 1 ? 0 : (hi == 2 ? 1 : 2));
+    return 4 + (lo == 2 ? 0 : lo == 1 ? (hi == 3 ? 1 : 2) : (hi == 3 ? 3 : (hi == 2 ? 4 : 5)));
+}
+
+// Reference gradient g at the nodes of one component with dofs v.
+template <int D, int P>
+__device__ inline void grad_nodes(const double (&v)[nsc(D, P)], double (&g)[grad_nv(D, P)][D]) {
+    static_assert(P == 1 || P == 2, "degree");
+    if constexpr (P == 1) {
+#pragma unroll
+        for (int a = 0; a < D; ++a) g[0][a] = v[a + 1] - v[0];
+    } else {
+        // d/d lambda_i at vertex k: 3 v_k for i = k, else 4 v_edge(k,i) - v_i
+#pragma unroll
+        for (int k = 0; k <= D; ++k) {
+            double b[D + 1];
+#pragma unroll
+            for (int i = 0; i <= D; ++i) b[i] = i == k ? 3.0 * v[k] : 4.0 * v[edge_dof<D>(k, i)] - v[i];
+#pragma unroll
+            for (int a = 0; a < D; ++a) g[k][a] = b[a + 1] - b[0];
+        }
+    }
+}
+
+// Its transpose: b[a] = sum_k q[k] . (reference gradient of phi_a at node k).
+template <int D, int P, typename T>
+__device__ inline void grad_nodes_t(const T (&q)[grad_nv(D, P)][D], T* b) {
+    static_assert(P == 1 || P == 2, "degree");
+#pragma unroll
+    for (int r = 0; r < nsc(D, P); ++r) b[r] = T(0);
+#pragma unroll
+    for (int k = 0; k < grad_nv(D, P); ++k) {
+        T y[D + 1];
+        y[0] = T(0);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            y[a + 1] = q[k][a];
+            y[0] -= q[k][a];
+        }
+#pragma unroll
+        for (int i = 0; i <= D; ++i) {
+            if (P == 1) {
+                b[i] += y[i];
+            } else if (i == k) {
+                b[k] += T(3) * y[k];
+            } else {
+                b[edge_dof<D>(k, i)] += T(4) * y[i];
+                b[i] -= y[i];
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------- split gathers
 // The gathers of one cell in two dependent stages, so that a persistent loop
 // can issue them for a later chunk while the current chunk is contracted.
@@ -544,14 +607,23 @@ __device__ inline void combine_clear(unsigned long long* keys, double* vals, int
     }
 }
 
+// First slot of a key: keys are hashed in groups of eight consecutive ones,
+// which keep their order inside the group, so that the flush finds
+// neighbouring dofs in neighbouring slots (both gradients of 2,058,000 P2
+// tetrahedra: 809 us with single keys hashed, 665 so).
+template <int TS>
+__device__ inline unsigned combine_hash(unsigned long long key) {
+    return ((unsigned)(((key >> 3) * 0x9E3779B97F4A7C15ull) >> 40) * 8u + (unsigned)(key & 7u)) & (TS - 1);
+}
+
 // The slot of a key, inserted if it is new; -1 if the probe limit is reached.
 template <int TS>
 __device__ inline int combine_slot(unsigned long long* keys, unsigned long long key) {
-    unsigned h = (unsigned)((key * 0x9E3779B97F4A7C15ull) >> 40) & (TS - 1);
+    unsigned h = combine_hash<TS>(key);
     for (int t = 0; t < 32; ++t) {
         const unsigned long long old = atomicCAS(&keys[h], kEmptyKey, key);
         if (old == kEmptyKey || old == key) return (int)h;
-        h = (h + 1) & (TS - 1);
+        h = (h + 8) & (TS - 1);
     }
     return -1;
 }
@@ -559,7 +631,7 @@ __device__ inline int combine_slot(unsigned long long* keys, unsigned long long 
 template <int NV, int TS>
 __device__ inline void combine_add(unsigned long long* keys, double* vals, unsigned long long key, const double* v,
                                    double* global_base) {
-    unsigned h = (unsigned)((key * 0x9E3779B97F4A7C15ull) >> 40) & (TS - 1);
+    unsigned h = combine_hash<TS>(key);
     for (int t = 0; t < 32; ++t) {
         const unsigned long long old = atomicCAS(&keys[h], kEmptyKey, key);
         if (old == kEmptyKey || old == key) {
@@ -567,23 +639,23 @@ __device__ inline void combine_add(unsigned long long* keys, double* vals, unsig
             for (int c = 0; c < NV; ++c) atomicAdd(&vals[h * NV + c], v[c]);
             return;
         }
-        h = (h + 1) & (TS - 1);
+        h = (h + 8) & (TS - 1);
     }
 #pragma unroll
     for (int c = 0; c < NV; ++c) atomicAdd(global_base + key * NV + c, v[c]);
 }
 
+// Lanes cover (slot, value) pairs: the values of a key, and those of
+// neighbouring slots with neighbouring keys, are consecutive addresses of one
+// atomic instruction and share its memory requests.
 template <int NV, int TS>
 __device__ inline void combine_flush(const unsigned long long* keys, const double* vals, double* global_base,
                                      int lane) {
-    for (int i = lane; i < TS; i += 64) {
-        const unsigned long long key = keys[i];
-        if (key == kEmptyKey) continue;
-#pragma unroll
-        for (int c = 0; c < NV; ++c) atomicAdd(global_base + key * NV + c, vals[i * NV + c]);
+    for (int i = lane; i < TS * NV; i += 64) {
+        const unsigned long long key = keys[i / NV];
+        if (key != kEmptyKey) atomicAdd(global_base + key * NV + i % NV, vals[i]);
     }
 }
-
 
 }  // namespace dev
 }  // namespace coffee

@@ -48,7 +48,7 @@ struct SvkArgs {
     int64_t ncells;
     FieldArg u;          // displacement, ncomp = D
     double mu, lambda;
-    const double* tab;   // W[nq] then dphi[D][nq][NS]
+    const double* tab;   // W[nq], dphi[D][nq][NS], then N[nq][NV]: the nodal basis of degree P - 1
     void* out;
     // reverse passes (energy; residual against lam)
     double seed;
@@ -116,66 +116,42 @@ __device__ inline void svk_S(const double (&F)[D][D], double mu, double lm, doub
         for (int j = 0; j < D; ++j) S[i][j] = (i == j ? lm * trE : 0.0) + 2.0 * mu * E[i][j];
 }
 
-// F, S, psi and P at point q from the reference displacement gradient, in
-// the arithmetic type T (FP64, or FP32 for the FP32 energy and residual).
-// E is formed from the displacement gradient H = grad u as (H + H^T + H^T H)/2,
-// which equals (F^T F - I)/2 without the cancellation of F^T F against I.
-template <int D, int NS, bool SC = false, typename T = double>
-__device__ inline void svk_point(const T (&uv)[NS * D], const T (&K)[D][D], const double* dphi_q, int nq, T mu,
-                                 T lm, T (&F)[D][D], T* psi, T (&Pout)[D][D]) {
-    T U[D][D];  // U[i][a] = sum_r u_{r,i} dphi_r/dX_a
-#pragma unroll
-    for (int i = 0; i < D; ++i)
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-            T s = T(0);
-#pragma unroll
-            for (int r = 0; r < NS; ++r) s += uv[r * D + i] * (T)tread<SC>(dphi_q + (size_t)a * nq * NS + r);
-            U[i][a] = s;
-        }
-    T H[D][D];
-#pragma unroll
-    for (int i = 0; i < D; ++i)
-#pragma unroll
-        for (int j = 0; j < D; ++j) {
-            T g = T(0);
-#pragma unroll
-            for (int a = 0; a < D; ++a) g += U[i][a] * K[a][j];
-            H[i][j] = g;
-            F[i][j] = (i == j ? T(1) : T(0)) + g;
-        }
+// psi and P = F S at a point with displacement gradient H = grad u, in the
+// arithmetic type T (FP64, or FP32 for the FP32 energy and residual). E is
+// formed as (H + H^T + H^T H)/2, which equals (F^T F - I)/2 without the
+// cancellation of F^T F against I.
+template <int D, typename T>
+__device__ inline void svk_point(const T (&H)[D][D], T mu, T lm, T* psi, T (&Pout)[D][D]) {
     T E[D][D], trE = T(0);
 #pragma unroll
     for (int i = 0; i < D; ++i)
 #pragma unroll
-        for (int j = 0; j < D; ++j) {
+        for (int j = i; j < D; ++j) {
             T t = H[i][j] + H[j][i];
 #pragma unroll
             for (int k = 0; k < D; ++k) t += H[k][i] * H[k][j];
-            E[i][j] = T(0.5) * t;
+            E[i][j] = E[j][i] = T(0.5) * t;
         }
 #pragma unroll
     for (int i = 0; i < D; ++i) trE += E[i][i];
+    T EE = T(0);
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+#pragma unroll
+        for (int j = 0; j < D; ++j) EE += E[i][j] * E[i][j];
+    *psi = T(0.5) * lm * trE * trE + mu * EE;
     T S[D][D];
 #pragma unroll
     for (int i = 0; i < D; ++i)
 #pragma unroll
         for (int j = 0; j < D; ++j) S[i][j] = (i == j ? lm * trE : T(0)) + T(2) * mu * E[i][j];
-    if (psi) {
-        T EE = T(0);
-#pragma unroll
-        for (int i = 0; i < D; ++i)
-#pragma unroll
-            for (int j = 0; j < D; ++j) EE += E[i][j] * E[i][j];
-        *psi = T(0.5) * lm * trE * trE + mu * EE;
-    }
 #pragma unroll
     for (int i = 0; i < D; ++i)
 #pragma unroll
         for (int j = 0; j < D; ++j) {
-            T t = T(0);
+            T t = S[i][j];
 #pragma unroll
-            for (int k = 0; k < D; ++k) t += F[i][k] * S[k][j];
+            for (int k = 0; k < D; ++k) t += H[i][k] * S[k][j];
             Pout[i][j] = t;
         }
 }
@@ -280,21 +256,31 @@ __device__ inline void svk_coord_bars(const double (&K)[D][D], const double (&Kb
 
 // MODE 0: energy, 1: residual, 2: reverse pass of the energy (coordinates),
 // 3: the reverse pass with the displacement gradient (the residual) too.
+//
+// One thread per cell. The displacement gradient has degree P - 1: it is
+// formed at its NV nodes once (H_k), a point takes H = sum_k N_k H_k and gives
+// back the moments Pm_k += w N_k P, so that the residual (Pm_k K^T against the
+// basis gradients at node k) and the coordinate bars (T = sum_k H_k^T Pm_k) are
+// formed once per cell: about 150 multiply-adds per point for P2 tetrahedra,
+// where going through the ten dofs at every point took 400 (energy and both
+// gradients through autograd, 2,058,000 cells: 1,282 -> 656 us together with
+// the group-hashed combining table; residual, 196,608 cells: 49 -> 36 us).
 template <int D, int P, int NQ, int MODE, typename OT>
 __global__ __launch_bounds__(256) void k_svk_vec(SvkArgs A) {
-    constexpr int NS = nsc(D, P);
+    constexpr int NS = nsc(D, P), NV = grad_nv(D, P);
     // arithmetic type of the point loop: the output type for the forward
     // energy and residual (FP32 mode computes them in FP32 from the FP64
-    // geometry), FP64 for the reverse pass
+    // geometry and node gradients), FP64 for the reverse pass
     using T = std::conditional_t<(MODE <= 1), OT, double>;
     // every table read below has the same address in all lanes: scalar path
     const double* W = A.tab;
-    const double* dphi = A.tab + NQ;
+    const double* Nk = A.tab + NQ + D * NQ * NS;
     // reverse pass: the scatter-adds (vertex coordinates; MODE 3 also the
     // displacement dofs) are combined per wave
     constexpr bool REV = MODE >= 2;                 // reverse pass
     constexpr bool RES = MODE == 1 || MODE == 3;    // residual (MODE 3: scattered into grad_u)
-    constexpr int TS = REV ? 256 : 1;
+    // 48 KB of tables with both gradients: three workgroups per CU
+    constexpr int TS = REV ? 128 : 1;
     constexpr int TU = MODE == 3 ? 256 : 1;
     __shared__ unsigned long long ckeys[4][TS], ukeys[4][TU];
     __shared__ double cvals[4][TS * D], uvals[4][TU * D];
@@ -311,85 +297,83 @@ __global__ __launch_bounds__(256) void k_svk_vec(SvkArgs A) {
             wave_sync();
         }
         Geom<D> g;
-        double uvd[NS * D];
+        T H[NV][D][D];  // displacement gradient at the nodes
         int vid[D + 1], uid[NS];
-        svk_load<D, NS>(A, cell, g, uvd, vid, uid);
-        T uv[NS * D], K[D][D];
+        {
+            double uvd[NS * D];
+            svk_load<D, NS>(A, cell, g, uvd, vid, uid);
 #pragma unroll
-        for (int i = 0; i < NS * D; ++i) uv[i] = (T)uvd[i];
+            for (int c = 0; c < D; ++c) {
+                double v[NS], gr[NV][D];
 #pragma unroll
-        for (int i = 0; i < D; ++i)
+                for (int r = 0; r < NS; ++r) v[r] = uvd[r * D + c];
+                grad_nodes<D, P>(v, gr);
 #pragma unroll
-            for (int j = 0; j < D; ++j) K[i][j] = (T)g.K[i][j];
-        T energy = T(0);
-        T res[RES ? D * NS : 1];
-        double Kbar[D][D];  // reverse pass: d Pi / d K
-        if constexpr (RES) {
+                for (int k = 0; k < NV; ++k)
 #pragma unroll
-            for (int i = 0; i < D * NS; ++i) res[i] = T(0);
+                    for (int j = 0; j < D; ++j) {
+                        double x = 0.0;
+#pragma unroll
+                        for (int a = 0; a < D; ++a) x += gr[k][a] * g.K[a][j];
+                        H[k][c][j] = (T)x;
+                    }
+            }
         }
-        if constexpr (REV) {
+        T energy = T(0);
+        T Pm[MODE > 0 ? NV : 1][D][D];
+#pragma unroll
+        for (int k = 0; k < (MODE > 0 ? NV : 1); ++k)
 #pragma unroll
             for (int i = 0; i < D; ++i)
 #pragma unroll
-                for (int j = 0; j < D; ++j) Kbar[i][j] = 0.0;
-        }
+                for (int j = 0; j < D; ++j) Pm[k][i][j] = T(0);
 #pragma unroll 1
         for (int q = 0; q < NQ; ++q) {
-            T Fm[D][D], psi, Pm[D][D];
-            svk_point<D, NS, true, T>(uv, K, dphi + q * NS, NQ, (T)A.mu, (T)A.lambda, Fm, &psi, Pm);
+            T n[NV], Hq[D][D], psi, Pq[D][D];
+#pragma unroll
+            for (int k = 0; k < NV; ++k) n[k] = (T)cload(Nk + q * NV + k);
+#pragma unroll
+            for (int i = 0; i < D; ++i)
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    T x = n[0] * H[0][i][j];
+#pragma unroll
+                    for (int k = 1; k < NV; ++k) x += n[k] * H[k][i][j];
+                    Hq[i][j] = x;
+                }
+            svk_point<D, T>(Hq, (T)A.mu, (T)A.lambda, &psi, Pq);
             const T wq = (T)cload(W + q);
             energy += wq * psi;
-            if constexpr (RES) {
-                // b_(c,a) += w sum_al (P K^T)_c,al dphi_a/dX_al
-                T Q[D][D];
+            if constexpr (MODE > 0) {
 #pragma unroll
-                for (int c = 0; c < D; ++c)
+                for (int k = 0; k < NV; ++k) {
+                    const T wn = wq * n[k];
 #pragma unroll
-                    for (int al = 0; al < D; ++al) {
-                        T t = T(0);
+                    for (int i = 0; i < D; ++i)
 #pragma unroll
-                        for (int j = 0; j < D; ++j) t += Pm[c][j] * K[al][j];
-                        Q[c][al] = wq * t;
-                    }
-#pragma unroll
-                for (int a = 0; a < NS; ++a) {
-                    T dp[D];
-#pragma unroll
-                    for (int al = 0; al < D; ++al) dp[al] = (T)cload(dphi + (size_t)al * NQ * NS + q * NS + a);
-#pragma unroll
-                    for (int c = 0; c < D; ++c) {
-                        T t = T(0);
-#pragma unroll
-                        for (int al = 0; al < D; ++al) t += Q[c][al] * dp[al];
-                        res[c * NS + a] += t;
-                    }
+                        for (int j = 0; j < D; ++j) Pm[k][i][j] += wn * Pq[i][j];
                 }
-            }
-            if constexpr (REV) {
-                // d Pi / d K[al][j] = |det J| sum_q w sum_i P_ij U_i,al
-                double U[D][D];
-#pragma unroll
-                for (int i = 0; i < D; ++i)
-#pragma unroll
-                    for (int al = 0; al < D; ++al) {
-                        double s = 0.0;
-#pragma unroll
-                        for (int r = 0; r < NS; ++r) s += uvd[r * D + i] * cload(dphi + (size_t)al * NQ * NS + q * NS + r);
-                        U[i][al] = s;
-                    }
-#pragma unroll
-                for (int al = 0; al < D; ++al)
-#pragma unroll
-                    for (int j = 0; j < D; ++j) {
-                        double s = 0.0;
-#pragma unroll
-                        for (int i = 0; i < D; ++i) s += Pm[i][j] * U[i][al];
-                        Kbar[al][j] += wq * s;
-                    }
             }
         }
         const double ad = g.adet;
+        T res[RES ? D * NS : 1];
+        if constexpr (RES) {
+            // b_(c,a) = sum_k (Pm_k K^T)_c . grad phi_a at node k
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                T Q[NV][D];
+#pragma unroll
+                for (int k = 0; k < NV; ++k)
+#pragma unroll
+                    for (int al = 0; al < D; ++al) {
+                        T t = T(0);
+#pragma unroll
+                        for (int j = 0; j < D; ++j) t += Pm[k][c][j] * (T)g.K[al][j];
+                        Q[k][al] = t;
+                    }
+                grad_nodes_t<D, P, T>(Q, res + c * NS);
+            }
+        }
         if constexpr (MODE == 0) {
             if (valid) reinterpret_cast<OT*>(A.out)[cell] = (OT)((T)ad * energy);
         } else if constexpr (MODE == 1) {
@@ -401,15 +385,35 @@ __global__ __launch_bounds__(256) void k_svk_vec(SvkArgs A) {
         } else {
             const double Pi = ad * energy;
             if (A.cell_value && valid) A.cell_value[cell] = Pi;
-            // Kbar scaled by |det J|; d Pi/d|det J| |det J| = Pi
+            // every term is linear in |det J| and H = (reference gradient) K:
+            // Jbar = (Pi I - |det J| sum_k H_k^T Pm_k) K^T, xbar_{j+1} = Jbar[:, j]
+            const double sd = A.seed;
+            double vx[D + 1][D], R[D][D];
 #pragma unroll
             for (int i = 0; i < D; ++i)
 #pragma unroll
-                for (int j = 0; j < D; ++j) Kbar[i][j] *= ad;
-            const double sd = A.seed;
+                for (int j = 0; j < D; ++j) {
+                    double t = 0.0;
+#pragma unroll
+                    for (int k = 0; k < NV; ++k)
+#pragma unroll
+                        for (int c = 0; c < D; ++c) t += H[k][c][i] * Pm[k][c][j];
+                    R[i][j] = (i == j ? Pi : 0.0) - ad * t;
+                }
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                double x0 = 0.0;
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    double t = 0.0;
+#pragma unroll
+                    for (int a = 0; a < D; ++a) t += R[i][a] * g.K[j][a];
+                    vx[j + 1][i] = sd * t;
+                    x0 -= t;
+                }
+                vx[0][i] = sd * x0;
+            }
             if (valid) {
-                double vx[D + 1][D];
-                svk_coord_bars<D>(g.K, Kbar, Pi, sd, vx);
                 svk_scatter_cell<D, NS, TS, TU, MODE == 3>(A, det, cell, vid, uid, vx, res, sd * ad, ckeys[wave],
                                                            cvals[wave], ukeys[wave], uvals[wave]);
             }
@@ -877,6 +881,11 @@ static coffee_status svk_table(int dev, int dim, int p, int q, const double** ou
         for (int k = 0; k < t.nq; ++k) h.push_back((double)t.W[k]);
         for (size_t i = 0; i < t.dphi.size(); ++i) h.push_back((double)t.dphi[i]);
     }
+    // the basis of degree p - 1 at the points (P1: the one value 1)
+    Tables nd;
+    if (!nd.init(dim, p - 1, t.q)) return COFFEE_E_INVALID_ARG;
+    for (int k = 0; k < (p == 1 ? 1 : nd.nq); ++k)
+        for (int i = 0; i < nd.n; ++i) h.push_back((double)nd.phi[(size_t)k * nd.n + i]);
     void* d = nullptr;
     if (hipMalloc(&d, h.size() * sizeof(double)) != hipSuccess) return COFFEE_E_NOMEM;
     if (hipMemcpy(d, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess) {

@@ -269,3 +269,48 @@ def test_autograd_energy_and_residual_action(cf):
     torch.cuda.synchronize()
     assert torch.allclose(coords.grad, gc2, rtol=1e-13, atol=1e-16)
     assert torch.allclose(dfs[0].values.grad, gu2[0], rtol=1e-13, atol=1e-16)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("d,p", [(3, 1), (3, 2), (2, 1), (2, 2)])
+def test_svk_energy_residual_ragged_counts(cf, oracle, d, p, prec):
+    """Energy and residual at counts around the 64-cell wave and the 256-cell workgroup, through a dof map and
+    cell-major."""
+    from gpu_util import TOL, assemble_gpu, cell_rel_err
+    rng = np.random.default_rng(190 + 10 * d + p)
+    mesh = I.make_mesh(d, 13 if d == 2 else 4, 0.1, rng)
+    u = _disp(mesh, p, rng)
+    cst = [1.2, 0.8]
+    for count in (1, 63, 64, 65, 257):
+        sub = I.Mesh(mesh.d, mesh.n, mesh.coords, np.ascontiguousarray(mesh.cells[:count]))
+        mapped = I.Field(u.values, np.ascontiguousarray(u.cell_to_dof[:count]), u.degree, u.ncomp)
+        cellmajor = I.Field(np.ascontiguousarray(u.values[mapped.cell_to_dof]), None, u.degree, u.ncomp)
+        for form in ("svk_energy", "svk_residual"):
+            ref = oracle.assemble(form, sub, p, fields=[mapped], constants=cst).reshape(count, -1)
+            for f in (mapped, cellmajor):
+                got = assemble_gpu(form, sub, p, [f], constants=cst, precision=prec).cpu().numpy().reshape(count, -1)
+                assert cell_rel_err(got, ref) < TOL[prec], (form, count, f.cell_to_dof is None)
+
+
+@pytest.mark.parametrize("d,p", [(3, 1), (3, 2), (2, 1), (2, 2)])
+def test_svk_energy_gradients_scattered_cells(cf, oracle, d, p):
+    """Both gradients with the cells in random order (more distinct dofs per wave than the combining tables hold) and
+    in mesh order, at counts around the wave and the workgroup, against the oracle's complex-step gradient."""
+    import torch
+    from gpu_util import to_dev
+    rng = np.random.default_rng(290 + 10 * d + p)
+    mesh = I.make_mesh(d, 17 if d == 2 else 5, 0.1, rng)
+    u = _disp(mesh, p, rng)
+    cst = [1.2, 0.8]
+    for order in (np.arange(mesh.ncells), rng.permutation(mesh.ncells)):
+        for count in (1, 65, 257, mesh.ncells):
+            sub = I.Mesh(d, mesh.n, mesh.coords, np.ascontiguousarray(mesh.cells[order[:count]]))
+            f = I.Field(u.values, np.ascontiguousarray(u.cell_to_dof[order[:count]]), u.degree, u.ncomp)
+            S, gc, gu = oracle.adjoint("svk_energy", sub, p, fields=[f], constants=cst)
+            coords, c2v, dfs = to_dev(sub, [f])
+            cv = torch.empty(count, dtype=torch.float64, device=coords.device)
+            hc, hu = cf.coffee_assemble_adjoint("svk_energy", d, p, coords, c2v, coeffs=dfs, constants=cst,
+                                                cell_value=cv)
+            for a, b in ((hc.cpu().numpy(), gc), (hu[0].cpu().numpy(), gu[0])):
+                assert np.abs(a - b).max() <= 1e-11 * np.abs(b).max(), count
+            assert abs(float(cv.sum()) - float(np.sum(S))) <= 1e-11 * abs(float(np.sum(S)))
