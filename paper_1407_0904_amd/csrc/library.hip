@@ -159,6 +159,17 @@ std::vector<char> pack_fragments(const RefTensor& R, int prec, bool sym, int row
 bool rtable_bytes(int form, int dim, int p, int q, int fd, int prec, std::vector<char>& buf) {
     RefTensor R;
     if (!build_reference(form, dim, p, q, fd, R)) return false;
+    if (uses_burgers_engine(form, p)) {
+        // the shared diagonal matrix (mass, stiffness, convection), then T
+        RefTensor T;
+        if (!build_node_mass(dim, p, q, T)) return false;
+        R.KR = 1 + dim * (dim + 1) / 2 + R.NS * dim;
+        R.R.resize((size_t)R.KR * R.NS * R.NS);
+        buf = pack_fragments(R, prec, false, R.NS);
+        const std::vector<char> t = pack_fragments(T, prec, false, T.NS);
+        buf.insert(buf.end(), t.begin(), t.end());
+        return true;
+    }
     // the cell-row engine reads plain 16-entry column tiles: one row group
     const int rpg = uses_elast_engine(form, dim, p, fd, prec) ? R.NS
                                                               : dev::vec_rows_per_group(R.NS, dev::vec_group_tiles(form, prec));

@@ -95,4 +95,21 @@ bool build_reference(int form, int dim, int p, int q, int fdeg, RefTensor& out) 
     return true;
 }
 
+bool build_node_mass(int dim, int p, int q, RefTensor& out) {
+    Tables sp, nd;
+    if (!sp.init(dim, p, q) || !nd.init(dim, p - 1, q)) return false;
+    const int n = sp.n;
+    out.NS = n;
+    out.KR = nd.n;
+    out.R.assign((size_t)nd.n * n * n, 0.0L);
+    for (int k = 0; k < nd.n; ++k)
+        for (int t = 0; t < sp.nq; ++t) {
+            const ld w = sp.W[t] * nd.phi[(size_t)t * nd.n + k];
+            for (int a = 0; a < n; ++a)
+                for (int b = 0; b < n; ++b)
+                    out.R[((size_t)k * n + a) * n + b] += w * sp.phi[(size_t)t * n + a] * sp.phi[(size_t)t * n + b];
+        }
+    return true;
+}
+
 }  // namespace coffee

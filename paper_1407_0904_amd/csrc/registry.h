@@ -5,6 +5,7 @@
 
 #include <vector>
 
+#include "burg.hpp"
 #include "elast.hpp"
 #include "linear.hpp"
 #include "scalar.hpp"
@@ -26,8 +27,9 @@ struct LinEntry {
 
 // Mass, Helmholtz and diffusion are symmetric single-block forms and use the symmetric
 // engine (scalar.hpp); elasticity uses the cell-row engine (elast.hpp) where its
-// ring of cell slots fits the LDS, the panel engine (vector.hpp) otherwise, and
-// Burgers the panel engine.
+// ring of cell slots fits the LDS, Burgers its own cell-row engine (burg.hpp) at
+// degrees 1 and 2; the rest (elasticity P3 tetrahedra, Burgers P3 triangles)
+// the panel engine (vector.hpp).
 constexpr bool uses_scalar_engine(int form) {
     return form == dev::F_MASS || form == dev::F_HELM || form == dev::F_DIFF;
 }
@@ -35,12 +37,16 @@ constexpr bool uses_elast_engine(int form, int d, int p, int fd, int prec) {
     return form == dev::F_ELAST && dev::el_sizes(d, p, fd, prec).fits;
 }
 
+constexpr bool uses_burgers_engine(int form, int p) { return form == dev::F_BURG && p <= 2; }
+
 template <int FORM, int D, int P, int FD, int PREC, int VAR = 0>
 const void* kernel_of() {
     if constexpr (uses_scalar_engine(FORM))
         return reinterpret_cast<const void*>(&dev::k_scalar<FORM, D, P, FD, PREC, VAR>);
     else if constexpr (uses_elast_engine(FORM, D, P, FD, PREC))
         return reinterpret_cast<const void*>(&dev::k_elast<D, P, FD, PREC>);
+    else if constexpr (uses_burgers_engine(FORM, P))
+        return reinterpret_cast<const void*>(&dev::k_burgers<D, P, PREC>);
     else
         return reinterpret_cast<const void*>(&dev::k_vector<FORM, D, P, FD, PREC>);
 }
@@ -58,6 +64,14 @@ hipError_t launch_linear(const dev::LinArgs& a, hipStream_t s, int grid) {
             hipFuncAttributeMaxDynamicSharedMemorySize, C::S.lds_bytes);
         if (attr != hipSuccess) return attr;
         hipLaunchKernelGGL((dev::k_elast<D, P, FD, PREC>), dim3(grid), dim3(C::WAVES * 64), C::S.lds_bytes, s, a);
+    } else if constexpr (uses_burgers_engine(FORM, P)) {
+        static_assert(FD == P, "state in the trial space");
+        using C = dev::BgCfg<D, P, PREC>;
+        static const hipError_t attr = hipFuncSetAttribute(
+            reinterpret_cast<const void*>(&dev::k_burgers<D, P, PREC>),
+            hipFuncAttributeMaxDynamicSharedMemorySize, C::S.lds_bytes);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((dev::k_burgers<D, P, PREC>), dim3(grid), dim3(C::WAVES * 64), C::S.lds_bytes, s, a);
     } else {
         using C = dev::VecCfg<FORM, D, P, FD, PREC>;
         static const hipError_t attr = hipFuncSetAttribute(
@@ -77,6 +91,10 @@ LinEntry lin_entry() {
                         kernel_of<FORM, D, P, FD, PREC, VAR>(), 256, 0, 256};
     } else if constexpr (uses_elast_engine(FORM, D, P, FD, PREC)) {
         using C = dev::ElCfg<D, P, FD, PREC>;
+        return LinEntry{FORM, D, P, FD, PREC, 0, &launch_linear<FORM, D, P, FD, PREC>, kernel_of<FORM, D, P, FD, PREC>(),
+                        C::WAVES * 64, C::S.lds_bytes, C::WAVES * 16};
+    } else if constexpr (uses_burgers_engine(FORM, P)) {
+        using C = dev::BgCfg<D, P, PREC>;
         return LinEntry{FORM, D, P, FD, PREC, 0, &launch_linear<FORM, D, P, FD, PREC>, kernel_of<FORM, D, P, FD, PREC>(),
                         C::WAVES * 64, C::S.lds_bytes, C::WAVES * 16};
     } else {

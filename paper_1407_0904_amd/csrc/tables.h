@@ -65,4 +65,9 @@ struct RefTensor {
 // fdeg: degree of the coefficient field (0 = no field / constants).
 bool build_reference(int form, int dim, int p, int q, int fdeg, RefTensor& out);
 
+// T_k[a][b] = sum_q W_q N_k phi_a phi_b, N_k the nodal basis of degree p - 1
+// (KR = its size): the mass tensors weighted by a function of that degree,
+// such as a component of the gradient of a degree-p field.
+bool build_node_mass(int dim, int p, int q, RefTensor& out);
+
 }  // namespace coffee

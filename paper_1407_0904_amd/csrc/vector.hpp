@@ -1,5 +1,7 @@
-// Device engine for the vector-valued bilinear forms (elasticity, Burgers
-// Jacobian): the element tensor of a cell is NC x NC blocks,
+// Device engine for the vector-valued bilinear forms that have no cell-row
+// engine (elasticity on P3 tetrahedra, Burgers on P3 triangles; elast.hpp and
+// burg.hpp take the others and share the gathers of this file): the element
+// tensor of a cell is NC x NC blocks,
 //     A[e][c n + a][c' n + b] = sum_k G_cc'[e][k] R[k][a n + b],
 // one shared reference tensor R and a per-cell, per-block geometry row G_cc'
 // (section 2, Fig. 1; the quadrature sum collapsed into R as in linear.hpp).

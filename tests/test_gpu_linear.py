@@ -335,3 +335,22 @@ def test_tile_shape_variants(cf, oracle, form, d, p, fd, prec, variant):
         cf.coffee_set_variant(-1)
     err = cell_rel_err(got, ref)
     assert err < TOL[prec], err
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("d,p,q", [(2, 1, -1), (2, 2, -1), (2, 2, 2), (3, 1, 1), (3, 2, 3), (3, 2, 16 + 5)])
+def test_burgers_cell_rows(cf, oracle, d, p, q, prec):
+    """Burgers at counts around the 16-cell unit and a workgroup's chunk, with rules that do not integrate the form
+    exactly (the diagonal matrix and the gradient part use the same rule), mapped and cell-major states."""
+    from gpu_util import TOL, assemble_gpu, cell_rel_err
+    rng = np.random.default_rng(400 + 10 * d + p)
+    mesh = I.make_mesh(d, 9 if d == 2 else 4, 0.12, rng)
+    w = _field_of_degree(mesh, p, rng, -1.0, 1.0, d)
+    cst = [0.7, 1.3]
+    for count in (1, 15, 16, 17, 64, 113, 129):
+        sub = I.Mesh(d, mesh.n, mesh.coords, np.ascontiguousarray(mesh.cells[:count]))
+        f = I.Field(w.values, np.ascontiguousarray(w.cell_to_dof[:count]), w.degree, w.ncomp)
+        ref = oracle.assemble("burgers", sub, p, q if q >= 0 else 2 * p + 1, fields=[f], constants=cst)
+        for g in (f, I.Field(np.ascontiguousarray(w.values[f.cell_to_dof]), None, f.degree, f.ncomp)):
+            got = assemble_gpu("burgers", sub, p, [g], constants=cst, quad_degree=q, precision=prec).cpu().numpy()
+            assert cell_rel_err(got, ref) < TOL[prec], (count, g.cell_to_dof is None)
