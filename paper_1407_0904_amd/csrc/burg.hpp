@@ -105,19 +105,6 @@ struct BgWave {
     int lane;
 };
 
-// Local dof of the P2 edge (k, i), i != k, for a k that is not a compile-time
-// constant.
-template <int D>
-__device__ inline int edge_dof_rt(int k, int i) {
-    int e = 0;
-#pragma unroll
-    for (int a = 0; a <= D; ++a)
-#pragma unroll
-        for (int b = 0; b <= D; ++b)
-            if (a != b) e = (k == a && i == b) ? edge_dof<D>(a, b) : e;
-    return e;
-}
-
 // D of the unit's cells into dbuf and the E rows into ebuf. Lane (cell, g)
 // holds the state at the dofs g, g + 4, ... and forms the D entries of those
 // dofs, then the gradient of the state at node g.

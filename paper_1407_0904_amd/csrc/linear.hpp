@@ -142,6 +142,19 @@ constexpr int edge_dof(int i, int j) {
     return 4 + (lo == 2 ? 0 : lo == 1 ? (hi == 3 ? 1 : 2) : (hi == 3 ? 3 : (hi == 2 ? 4 : 5)));
 }
 
+// Local dof of the P2 edge (k, i), i != k, for a k that is not a compile-time
+// constant.
+template <int D>
+__device__ inline int edge_dof_rt(int k, int i) {
+    int e = 0;
+#pragma unroll
+    for (int a = 0; a <= D; ++a)
+#pragma unroll
+        for (int b = 0; b <= D; ++b)
+            if (a != b) e = (k == a && i == b) ? edge_dof<D>(a, b) : e;
+    return e;
+}
+
 // Reference gradient g at the nodes of one component with dofs v.
 template <int D, int P>
 __device__ inline void grad_nodes(const double (&v)[nsc(D, P)], double (&g)[grad_nv(D, P)][D]) {

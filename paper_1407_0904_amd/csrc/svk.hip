@@ -844,9 +844,463 @@ __global__ __launch_bounds__(256, 2) void k_svk_jac(SvkArgs A) {
     }
 }
 
+// ---------------------------------------------------------------- Jacobian, degree 2
+// At degree 2 the tangent in reference coordinates,
+//     H_cc' = lambda k_c k_c'^T + mu k_c' k_c^T + mu (F_c . F_c') K K^T + delta_cc' K S K^T,   k_c = K F_c,
+// is a quadratic function on the cell (F is linear), and the gradient of a
+// basis function is linear: phi_v gives (4 lambda_v - 1) grad lambda_v, the
+// function of edge (i, n) gives 4 lambda_n grad lambda_i + 4 lambda_i grad lambda_n.
+// With H_ij = grad lambda_i . H grad lambda_j = sum_vw lambda_v lambda_w h^vw (h
+// symmetric in v, w), a block's entries are sums of the moments
+//     int (4 lambda_n - d_ni) (4 lambda_q - d_qj) H_ij,
+// one for each pair of (i, n) (the vertex i if n = i, else the edge (i, n))
+// and (j, q). The moments of barycentric monomials, int prod lambda_v^m_v =
+// prod m_v! / (d + sum m_v)! on the reference cell, give with C = sum_vw h^vw +
+// sum_v h^vv and r_n = 2 sum_w h^nw + 2 h^nn, in units of 1 / (d + 4)!,
+//     int lambda_n lambda_q H = (1 + d_nq) (C + r_n + r_q + 2 h^nq),
+//     int lambda_n H = (d + 4) (C + r_n),   int H = (d + 3) (d + 4) C.
+// The integrand has degree 4, so this equals the sum over every rule of that
+// degree (the only ones the entry point takes for this form). A lane runs
+// about 2,300 FP64 operations for half a block of a P2 tetrahedron, where the
+// sum over the 14 points took 3,600 (196,608 cells: FP64 572 -> 480 us, FP32
+// 456 -> 433). It is bound by its instructions: of the 25,000 cycles a group
+// of five cells takes, 9,800 go to the block, 7,600 to the geometry and the
+// shared coefficients, 6,700 to staging and stores. Two waves per SIMD (the
+// k_c read from LDS where used, two cells staged at a time) ran 548 us: 64
+// registers spilled, and the instructions are the same. Triangles, whose
+// blocks have 36 entries, stay with the point kernel (62 us against 97).
+//
+// Work layout: a wave takes CPW consecutive cells; lane (cell, block c <= c',
+// half). Tetrahedra split a block's columns in halves {v0, v1, e01, e02, e13}
+// and its image under the vertex permutation 0 -> 2, 1 -> 3, 2 -> 1, 3 -> 0, so
+// that both halves run the same code on permuted data (50 accumulators each;
+// triangles keep the 36 of a block in one lane). The cell's lanes load its
+// dofs, form m_c = K K^T (reference gradient of u_c) and k_c = K e_c + m_c
+// at the vertices, F_c . F_c' and the K S K^T coefficients together in LDS; the whole
+// tensors are staged over that and leave as one contiguous range of 16-byte
+// stores. The next group's gathers are in flight meanwhile.
+template <int D>
+struct SvkJ2 {
+    static constexpr int V = D + 1, NS = nsc(D, 2), N = D * NS, NB = D * (D + 1) / 2;
+    static constexpr int SPLIT = D == 3 ? 2 : 1;
+    static constexpr int LPC = NB * SPLIT, CPW = 64 / LPC;
+    static constexpr int NP = V * (V + 1) / 2;       // pairs n <= l, also i <= j
+    static constexpr int NCOL = D == 3 ? 5 : NS;     // columns per lane
+    static constexpr int RL = (NS + LPC - 1) / LPC;  // dofs a lane loads
+    // LDS of one cell, in doubles
+    static constexpr int X = 0, U = X + V * D, MM = U + NS * D, GG = MM + D * V * V, HH = GG + D * V * D,
+                         KB = HH + D * V * D, MB = KB + V * D, SB = MB + NP, KF = SB + NP * NP, PH = KF + D * V * V,
+                         CELL = (PH + NB * NP) | 1;
+    // column of the lane's half for (j, q), -1 if it is not one of them
+    static constexpr int col(int j, int q) {
+        if (D == 2) return j == q ? j : edge_dof<2>(j, q);
+        const int lo = j < q ? j : q, hi = j < q ? q : j;
+        if (lo == hi) return lo < 2 ? lo : -1;
+        return lo == 0 && hi == 1 ? 2 : (lo == 0 && hi == 2 ? 3 : (lo == 1 && hi == 3 ? 4 : -1));
+    }
+    static constexpr int row(int i, int n) { return i == n ? i : edge_dof<D>(i, n); }
+    static constexpr int pair(int a, int b) {
+        const int lo = a < b ? a : b, hi = a < b ? b : a;
+        return lo * V - lo * (lo - 1) / 2 + hi - lo;
+    }
+    template <typename OT>
+    static constexpr int wave_bytes() {
+        const int a = CPW * CELL * 8, b = CPW * N * N * (int)sizeof(OT);
+        return ((a > b ? a : b) + 15) / 16 * 16;
+    }
+};
+
+// f(0), ..., f(N - 1) with compile-time arguments (a loop whose unrolling
+// would exceed the compiler's limit would leave the accumulators in memory).
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        static_for<N, I + 1>(f);
+    }
+}
+
+template <int V>
+__device__ inline int pair_rt(int a, int b) {
+    const int lo = a < b ? a : b, hi = a < b ? b : a;
+    return lo * V - lo * (lo - 1) / 2 + hi - lo;
+}
+
+template <int D, typename OT>
+__global__ __launch_bounds__(256, 1) void k_svk_jac2(SvkArgs A) {
+    using C = SvkJ2<D>;
+    constexpr int V = C::V, NS = C::NS, N = C::N, NB = C::NB, LPC = C::LPC, CPW = C::CPW, NP = C::NP, RL = C::RL;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double* wl = reinterpret_cast<double*>(lds + wave * C::template wave_bytes<OT>());
+    const int cl = lane / LPC < CPW ? lane / LPC : CPW - 1, k = lane % LPC;
+    const bool owner = lane < CPW * LPC;
+    double* cc = wl + cl * C::CELL;
+    const double mu = A.mu, lm = A.lambda;
+    // dofs of the permuted pairs (i, n), four bits each; and the pairs' own numbers
+    uint64_t dofs4 = 0, pairs4 = 0;
+    {
+        const int half = k / NB;
+        int pi[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) pi[v] = half == 0 ? v : (v < 2 ? v + 2 : 3 - v);
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+#pragma unroll
+            for (int n = i; n < V; ++n) {
+                const int d = i == n ? pi[i] : edge_dof_rt<D>(pi[i], pi[n]);
+                dofs4 |= (uint64_t)d << (4 * C::pair(i, n));
+                pairs4 |= (uint64_t)pair_rt<V>(pi[i], pi[n]) << (4 * C::pair(i, n));
+            }
+    }
+    // gathers of a group: lane k of a cell takes vertex k and the dofs k, k + LPC, ...
+    const int64_t ngroups = (A.ncells + CPW - 1) / CPW;
+    const int64_t nwaves = (int64_t)gridDim.x * 4;
+    int vid = 0, uid[RL];
+    double xr[D], ur[RL][D];
+    auto cell_of = [&](int64_t g) -> int64_t {
+        const int64_t c = g * CPW + cl;
+        return c < A.ncells ? c : A.ncells - 1;
+    };
+    auto load_ids = [&](int64_t g) {
+        const int64_t c = cell_of(g);
+        vid = A.c2v[c * V + (k < V ? k : 0)];
+        if (A.u.map) {
+#pragma unroll
+            for (int t = 0; t < RL; ++t) uid[t] = A.u.map[c * NS + (k + t * LPC < NS ? k + t * LPC : 0)];
+        }
+    };
+    auto load_vals = [&](int64_t g) {
+        const int64_t c = cell_of(g);
+#pragma unroll
+        for (int i = 0; i < D; ++i) xr[i] = A.coords[(int64_t)vid * D + i];
+#pragma unroll
+        for (int t = 0; t < RL; ++t) {
+            const int r = k + t * LPC < NS ? k + t * LPC : 0;
+            const int64_t at = A.u.map ? (int64_t)uid[t] * D : (c * NS + r) * D;
+#pragma unroll
+            for (int i = 0; i < D; ++i) ur[t][i] = A.u.values[at + i];
+        }
+    };
+    int64_t grp = (int64_t)blockIdx.x * 4 + wave;
+    if (grp >= ngroups) return;  // wave-uniform; no workgroup barrier follows
+    load_ids(grp);
+    load_vals(grp);
+    load_ids(grp + nwaves < ngroups ? grp + nwaves : grp);
+    for (; grp < ngroups; grp += nwaves) {
+        // the lane's place in its cell, read again opaquely for every group:
+        // the LDS offsets that follow from it are formed where they are used
+        // instead of being kept across the loop (hundreds of registers)
+        int kk = lane % LPC;
+        asm volatile("" : "+v"(kk));
+        const int blk = kk % NB, half = kk / NB;
+        int c1 = 0, c2 = 0;
+        {
+            int t = blk;
+            while (t >= D - c1) { t -= D - c1; ++c1; }
+            c2 = c1 + t;
+        }
+        const double dg = c1 == c2 ? 1.0 : 0.0, dg2 = 2.0 * dg;
+        // vertex permutation of the half, pairs of permuted vertices
+        int pi[V], pr[NP];
+#pragma unroll
+        for (int v = 0; v < V; ++v) pi[v] = half == 0 ? v : (v < 2 ? v + 2 : 3 - v);
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int w = v; w < V; ++w) pr[C::pair(v, w)] = (int)((pairs4 >> (4 * C::pair(v, w))) & 15);
+        // the cell's vertices and dofs to LDS; the next group's gathers
+        if (owner) {
+            if (k < V) {
+#pragma unroll
+                for (int i = 0; i < D; ++i) cc[C::X + k * D + i] = xr[i];
+            }
+#pragma unroll
+            for (int t = 0; t < RL; ++t)
+                if (k + t * LPC < NS) {
+#pragma unroll
+                    for (int i = 0; i < D; ++i) cc[C::U + (k + t * LPC) * D + i] = ur[t][i];
+                }
+        }
+        const int64_t n1 = grp + nwaves < ngroups ? grp + nwaves : grp;
+        const int64_t n2 = grp + 2 * nwaves < ngroups ? grp + 2 * nwaves : n1;
+        load_vals(n1);
+        load_ids(n2);
+        wave_sync();
+        Geom<D> g;
+        {
+            double x[V][D];
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+#pragma unroll
+                for (int i = 0; i < D; ++i) x[v][i] = cc[C::X + v * D + i];
+            geometry_from_coords<D>(x, g);
+        }
+        const double scale = g.adet * (D == 2 ? 16.0 / 720.0 : 16.0 / 5040.0);  // 16 |det J| / (D + 4)!
+        if (owner && k < D) {
+            // component k: reference gradient (GG), physical gradient (HH) and
+            // m = K K^T (reference gradient) in barycentric components (MM) at the vertices
+            double v[NS], gr[V][D], kc[D];  // kc: column k of K
+#pragma unroll
+            for (int a = 0; a < D; ++a) {
+                kc[a] = g.K[a][0];
+#pragma unroll
+                for (int e = 1; e < D; ++e) kc[a] = k == e ? g.K[a][e] : kc[a];
+            }
+#pragma unroll
+            for (int r = 0; r < NS; ++r) v[r] = cc[C::U + r * D + k];
+            grad_nodes<D, 2>(v, gr);
+#pragma unroll
+            for (int n = 0; n < V; ++n) {
+                double h[D], y0 = 0.0, z0 = 0.0;
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    double t = 0.0;
+#pragma unroll
+                    for (int a = 0; a < D; ++a) t += gr[n][a] * g.K[a][j];
+                    h[j] = t;
+                    cc[C::HH + (k * V + n) * D + j] = t;
+                    cc[C::GG + (k * V + n) * D + j] = gr[n][j];
+                }
+#pragma unroll
+                for (int a = 0; a < D; ++a) {
+                    double t = 0.0;
+#pragma unroll
+                    for (int j = 0; j < D; ++j) t += g.K[a][j] * h[j];
+                    cc[C::MM + (k * V + n) * V + a + 1] = t;
+                    cc[C::KF + (k * V + n) * V + a + 1] = kc[a] + t;
+                    y0 -= t;
+                    z0 -= kc[a] + t;
+                }
+                cc[C::MM + (k * V + n) * V] = y0;
+                cc[C::KF + (k * V + n) * V] = z0;
+            }
+        }
+        if (owner && k == LPC - 1) {
+            // barycentric rows of K and their products
+            double kb[V][D];
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                double t = 0.0;
+#pragma unroll
+                for (int a = 0; a < D; ++a) {
+                    kb[a + 1][j] = g.K[a][j];
+                    t -= g.K[a][j];
+                }
+                kb[0][j] = t;
+            }
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+#pragma unroll
+                for (int j = 0; j < D; ++j) cc[C::KB + i * D + j] = kb[i][j];
+#pragma unroll
+                for (int j = i; j < V; ++j) {
+                    double t = 0.0;
+#pragma unroll
+                    for (int a = 0; a < D; ++a) t += kb[i][a] * kb[j][a];
+                    cc[C::MB + C::pair(i, j)] = t;
+                }
+            }
+        }
+        wave_sync();
+        // for the pair (v, w): the coefficient of tr E = sum_e H_ee + |H_e|^2 / 2, then those of
+        // (K S K^T)_ij = lambda tr E (K K^T)_ij + mu sum_e (K_ie m_e,j + m_e,i K_je + m_e,i m_e,j)
+#pragma unroll 1
+        for (int p = kk; owner && p < NP; p += LPC) {
+            int v = 0, w = p;
+            while (w >= V - v) { w -= V - v; ++v; }
+            w += v;
+            double mv[D][V], mw[D][V], tau = 0.0;
+#pragma unroll
+            for (int e = 0; e < D; ++e) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    mv[e][i] = cc[C::MM + (e * V + v) * V + i];
+                    mw[e][i] = cc[C::MM + (e * V + w) * V + i];
+                }
+                double x = 0.0;
+#pragma unroll
+                for (int a = 0; a < D; ++a)
+                    x += cc[C::GG + (e * V + v) * D + a] * mw[e][a + 1] + cc[C::GG + (e * V + w) * D + a] * mv[e][a + 1];
+                tau += 0.5 * (cc[C::HH + (e * V + v) * D + e] + cc[C::HH + (e * V + w) * D + e]) + 0.25 * x;
+            }
+            // mu F_c . F_c' (twice the coefficient for v < w, as e_nl below)
+            {
+                double gv[D][D], gw[D][D], hh[D][D];
+#pragma unroll
+                for (int e = 0; e < D; ++e)
+#pragma unroll
+                    for (int a = 0; a < D; ++a) {
+                        gv[e][a] = cc[C::GG + (e * V + v) * D + a];
+                        gw[e][a] = cc[C::GG + (e * V + w) * D + a];
+                        hh[e][a] = cc[C::HH + (e * V + v) * D + a] + cc[C::HH + (e * V + w) * D + a];
+                    }
+                const double f2 = v == w ? 0.5 * mu : mu;
+                int blk2 = 0;
+#pragma unroll
+                for (int a = 0; a < D; ++a)
+#pragma unroll
+                    for (int b = a; b < D; ++b, ++blk2) {
+                        double x = hh[a][b] + hh[b][a];
+#pragma unroll
+                        for (int t = 0; t < D; ++t) x += gv[a][t] * mw[b][t + 1] + gw[a][t] * mv[b][t + 1];
+                        cc[C::PH + blk2 * NP + p] = f2 * ((a == b ? 2.0 : 0.0) + x);
+                    }
+            }
+#pragma unroll
+            for (int i = 0; i < V; ++i)
+#pragma unroll
+                for (int j = i; j < V; ++j) {
+                    double x = 0.0;
+#pragma unroll
+                    for (int e = 0; e < D; ++e)
+                        x += cc[C::KB + i * D + e] * (mv[e][j] + mw[e][j]) + cc[C::KB + j * D + e] * (mv[e][i] + mw[e][i]) +
+                             mv[e][i] * mw[e][j] + mw[e][i] * mv[e][j];
+                    cc[C::SB + C::pair(i, j) * NP + p] = lm * tau * cc[C::MB + C::pair(i, j)] + 0.5 * mu * x;
+                }
+        }
+        wave_sync();
+        // this lane's k_c1, k_c2 at the (permuted) vertices, mu (F_c1 . F_c2)
+        double f[V][V], q2[V][V], ph[NP];
+#pragma unroll
+        for (int n = 0; n < V; ++n) {
+            const double *fn = cc + C::KF + (c1 * V + pi[n]) * V, *qn = cc + C::KF + (c2 * V + pi[n]) * V;
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                f[n][i] = fn[pi[i]];
+                q2[n][i] = qn[pi[i]];
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) ph[p] = cc[C::PH + blk * NP + pr[p]];
+        double acc[NS][C::NCOL];
+#pragma unroll
+        for (int a = 0; a < NS; ++a)
+#pragma unroll
+            for (int b = 0; b < C::NCOL; ++b) acc[a][b] = 0.0;
+        static_for<V>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            double lf[V], mg[V];
+#pragma unroll
+            for (int n = 0; n < V; ++n) {
+                lf[n] = lm * f[n][i];
+                mg[n] = mu * q2[n][i];
+            }
+            // the gradients of the barycentric coordinates sum to zero: j = 0
+            // is minus the sum of the others, formed last
+            double hs[V], es[V][V], rs[V], cs = 0.0;
+#pragma unroll
+            for (int n = 0; n < V; ++n) {
+                hs[n] = rs[n] = 0.0;
+#pragma unroll
+                for (int l = 0; l < V; ++l) es[n][l] = 0.0;
+            }
+            static_for<V>([&](auto jc) __attribute__((always_inline)) {
+                constexpr int j = (decltype(jc)::value + 1) % V;
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                // e_nl = 2 h^nl (n < l), hd_n = h^nn
+                double hd[V], e[V][V], rn[V], Cs = 0.0;
+                if constexpr (j != 0) {
+                    const int ij = pr[C::pair(i, j)];
+                    const double* sbij = cc + C::SB + ij * NP;
+                    const double mij = cc[C::MB + ij];
+#pragma unroll
+                    for (int n = 0; n < V; ++n) {
+                        hd[n] = lf[n] * q2[n][j] + mg[n] * f[n][j] + ph[C::pair(n, n)] * mij + dg * sbij[pr[C::pair(n, n)]];
+                        rn[n] = 4.0 * hd[n];
+                        Cs += 2.0 * hd[n];
+                        hs[n] -= hd[n];
+                    }
+#pragma unroll
+                    for (int n = 0; n < V; ++n)
+#pragma unroll
+                        for (int l = n + 1; l < V; ++l) {
+                            const double x = lf[n] * q2[l][j] + mg[n] * f[l][j] + lf[l] * q2[n][j] + mg[l] * f[n][j] +
+                                             ph[C::pair(n, l)] * mij + dg2 * sbij[pr[C::pair(n, l)]];
+                            e[n][l] = e[l][n] = x;
+                            rn[n] += x;
+                            rn[l] += x;
+                            Cs += x;
+                            es[n][l] -= x;
+                            es[l][n] = es[n][l];
+                        }
+#pragma unroll
+                    for (int n = 0; n < V; ++n) rs[n] -= rn[n];
+                    cs -= Cs;
+                } else {
+                    Cs = cs;
+#pragma unroll
+                    for (int n = 0; n < V; ++n) {
+                        hd[n] = hs[n];
+                        rn[n] = rs[n];
+#pragma unroll
+                        for (int l = 0; l < V; ++l) e[n][l] = es[n][l];
+                    }
+                }
+                static_for<V * V>([&](auto nq) __attribute__((always_inline)) {
+                    constexpr int n = decltype(nq)::value / V, q = decltype(nq)::value % V;
+                    if constexpr (C::col(j, q) >= 0) {
+                        double w = n == q ? 2.0 * (Cs + 2.0 * rn[n] + 2.0 * hd[n]) : Cs + rn[n] + rn[q] + e[n][q];
+                        if (n == i) w -= 0.25 * (D + 4) * (Cs + rn[q]);
+                        if (q == j) w -= 0.25 * (D + 4) * (Cs + rn[n]);
+                        if (n == i && q == j) w += 0.0625 * (D + 3) * (D + 4) * Cs;
+                        acc[C::row(i, n)][C::col(j, q)] += w;
+                        // in order: left free, the sums of all (i, j) are kept apart until the end
+                        asm volatile("" : "+v"(acc[C::row(i, n)][C::col(j, q)]));
+                    }
+                });
+            });
+        });
+        wave_sync();
+        // stage the group's tensors and write them
+        if (owner) {
+            asm volatile("" : "+v"(dofs4));
+            // element offsets: upper block at (rd, cd), its transpose at (cd, rd)
+            OT* up = reinterpret_cast<OT*>(wl) + cl * N * N + c1 * NS * N + c2 * NS;
+            OT* lo = reinterpret_cast<OT*>(wl) + cl * N * N + c2 * NS * N + c1 * NS;
+            int cd[C::NCOL];
+            static_for<V * V>([&](auto jq) __attribute__((always_inline)) {
+                constexpr int j = decltype(jq)::value / V, q = decltype(jq)::value % V;
+                if constexpr (j <= q && C::col(j, q) >= 0) cd[C::col(j, q)] = (int)((dofs4 >> (4 * C::pair(j, q))) & 15);
+            });
+            static_for<V * V>([&](auto in) __attribute__((always_inline)) {
+                constexpr int i = decltype(in)::value / V, n = decltype(in)::value % V;
+                if constexpr (i <= n) {
+                    const int rd = (int)((dofs4 >> (4 * C::pair(i, n))) & 15);
+                    OT *ur = up + rd * N, *lr = lo + rd;
+#pragma unroll
+                    for (int b = 0; b < C::NCOL; ++b) acc[C::row(i, n)][b] *= scale;
+#pragma unroll
+                    for (int b = 0; b < C::NCOL; ++b) ur[cd[b]] = (OT)acc[C::row(i, n)][b];
+                    if (c1 != c2) {
+#pragma unroll
+                        for (int b = 0; b < C::NCOL; ++b) lr[cd[b] * N] = (OT)acc[C::row(i, n)][b];
+                    }
+                }
+            });
+        }
+        wave_sync();
+        const int64_t c0 = grp * CPW;
+        const int nc = A.ncells - c0 < CPW ? (int)(A.ncells - c0) : CPW;
+        constexpr int CPC = N * N * (int)sizeof(OT) / 16;  // 16-byte chunks per cell
+        static_assert(N * N * sizeof(OT) % 16 == 0, "whole cells in 16-byte stores");
+        const svk_u32x4* s4 = reinterpret_cast<const svk_u32x4*>(wl);
+        svk_u32x4* o4 = reinterpret_cast<svk_u32x4*>(A.out) + c0 * CPC;
+        const int nv = nc * CPC;
+#pragma unroll
+        for (int e0 = 0; e0 < CPW * CPC; e0 += 64)
+            if (e0 + lane < nv) gstore_nt(&o4[e0 + lane], s4[e0 + lane]);
+        wave_sync();
+    }
+}
+
 }  // namespace dev
 
 // ---------------------------------------------------------------- host side
+
+// workgroups of the degree-2 Jacobian per CU
+constexpr int kJac2Grid = 4;
 
 static std::mutex g_svk_mu;
 static std::map<std::tuple<int, int, int, int>, void*> g_svk_tabs;  // (dev, dim, p, q)
@@ -910,6 +1364,20 @@ namespace {
 
 constexpr int svk_jac_slices(int, int p) { return p == 2 ? 2 : 1; }
 
+template <int D, typename OT>
+hipError_t launch_jac2(const dev::SvkArgs& a, hipStream_t s, int ncu) {
+    using C = dev::SvkJ2<D>;
+    constexpr int lds = 4 * C::template wave_bytes<OT>();
+    static_assert(lds <= 160 * 1024, "LDS");
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&dev::k_svk_jac2<D, OT>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return attr;
+    const int64_t groups = (a.ncells + C::CPW - 1) / C::CPW;
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((groups + 3) / 4, (int64_t)ncu * kJac2Grid));
+    hipLaunchKernelGGL((dev::k_svk_jac2<D, OT>), dim3(grid), dim3(256), lds, s, a);
+    return hipGetLastError();
+}
+
 // compiled set: triangles and tetrahedra, P1 (q = 2, evaluated at one point
 // with the summed weight) and P2 (q = 4)
 template <int D, int P, int NQ>
@@ -933,14 +1401,16 @@ hipError_t launch_svk(int form, int precision, const dev::SvkArgs& a, hipStream_
         if (f64) hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 1, double>), dim3(grid), dim3(256), 0, s, a);
         else hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 1, float>), dim3(grid), dim3(256), 0, s, a);
     } else {
-        // row slices per block: enough to keep the accumulators of a P2
-        // tetrahedron block well under the register file of 2 waves per SIMD
+        if constexpr (P == 2 && D == 3)
+            return f64 ? launch_jac2<D, double>(a, s, ncu) : launch_jac2<D, float>(a, s, ncu);
         constexpr int AH = svk_jac_slices(D, P);
         constexpr int CPW = 64 / (D * (D + 1) / 2 * AH);
         const int64_t waves = (a.ncells + CPW - 1) / CPW;
         const int g2 = (int)std::max<int64_t>(1, std::min<int64_t>((waves + 3) / 4, (int64_t)ncu * 16));
-        if (f64) hipLaunchKernelGGL((dev::k_svk_jac<D, P, NQ, double, AH>), dim3(g2), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((dev::k_svk_jac<D, P, NQ, float, AH>), dim3(g2), dim3(256), 0, s, a);
+        if constexpr (P == 1 || D == 2) {
+            if (f64) hipLaunchKernelGGL((dev::k_svk_jac<D, P, NQ, double, AH>), dim3(g2), dim3(256), 0, s, a);
+            else hipLaunchKernelGGL((dev::k_svk_jac<D, P, NQ, float, AH>), dim3(g2), dim3(256), 0, s, a);
+        }
     }
     return hipGetLastError();
 }

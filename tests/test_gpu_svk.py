@@ -314,3 +314,23 @@ def test_svk_energy_gradients_scattered_cells(cf, oracle, d, p):
             for a, b in ((hc.cpu().numpy(), gc), (hu[0].cpu().numpy(), gu[0])):
                 assert np.abs(a - b).max() <= 1e-11 * np.abs(b).max(), count
             assert abs(float(cv.sum()) - float(np.sum(S))) <= 1e-11 * abs(float(np.sum(S)))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("d,p", [(3, 1), (3, 2), (2, 2)])
+def test_svk_jacobian_ragged_counts(cf, oracle, d, p, prec):
+    """Jacobian at counts around the five-cell group and the twenty cells of a workgroup, through a dof map and
+    cell-major, with large displacements (every term of the tangent matters)."""
+    from gpu_util import TOL, assemble_gpu, cell_rel_err
+    rng = np.random.default_rng(390 + 10 * d + p)
+    mesh = I.make_mesh(d, 9 if d == 2 else 4, 0.1, rng)
+    u = _disp(mesh, p, rng, sigma=0.2)
+    cst = [1.2, 0.8]
+    for count in (1, 4, 5, 6, 19, 20, 21, 101):
+        sub = I.Mesh(mesh.d, mesh.n, mesh.coords, np.ascontiguousarray(mesh.cells[:count]))
+        mapped = I.Field(u.values, np.ascontiguousarray(u.cell_to_dof[:count]), u.degree, u.ncomp)
+        cellmajor = I.Field(np.ascontiguousarray(u.values[mapped.cell_to_dof]), None, u.degree, u.ncomp)
+        ref = oracle.assemble("svk_jacobian", sub, p, fields=[mapped], constants=cst)
+        for f in (mapped, cellmajor):
+            got = assemble_gpu("svk_jacobian", sub, p, [f], constants=cst, precision=prec).cpu().numpy()
+            assert cell_rel_err(got, ref) < TOL[prec], (count, f.cell_to_dof is None)
