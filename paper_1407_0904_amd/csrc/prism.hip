@@ -23,8 +23,9 @@
 // in FP64 at its points and writes those G entries to the tile's LDS rows.
 // The MFMA loop then runs over all n-tiles at once, and the 16 element
 // matrices leave through LDS as contiguous 16-byte stores (the staging area
-// reuses the G rows). Degrees 2 and 3 (k_prism_big): the waves of a
-// workgroup share 32 cells, each wave taking a share of the n-tiles.
+// reuses the G rows). Degrees 2 and 3 (k_prism_fac): the contraction is
+// factored over the triangle and the interval, the waves of a workgroup share
+// 32 cells, each taking pairs of interval dofs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -71,8 +72,8 @@ struct PrismCfg {
     // two waves per workgroup when four would take more than half the LDS
     static constexpr int WAVES = 4 * WAVE_BYTES <= 80 * 1024 ? 4 : 2;
     static constexpr int LDS_BYTES = WAVES * WAVE_BYTES;
-    static constexpr int REGB = NT * KS * (PREC == PREC_F64 ? 2 : (PREC == PREC_F32 ? 1 : 4));
-    static constexpr bool RREG = REGB <= 64;  // reference fragments held in registers
+    // the reference fragments are held in registers
+    static_assert(NT * KS * (PREC == PREC_F64 ? 2 : (PREC == PREC_F32 ? 1 : 4)) <= 64, "registers");
 };
 
 // Word 3 of a raw buffer resource on gfx9-family chips: 32-bit data format
@@ -98,7 +99,7 @@ struct PrismArgs {
     int64_t ncells;
     FieldArg f;            // degree-1 prism field (6 dofs per cell); values NULL: none
     double kdt;            // kappa dt (diffusion)
-    const double* qtab;    // [NQ][4]: X, Y, Z, W
+    const double* qtab;    // [NQ][4]: X, Y, Z, W; degrees 2, 3: then the interval weights
     const void* rfrag;     // packed reference fragments
     void* out;
     int64_t ntiles;        // ceil(ncells / 16)
@@ -202,24 +203,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         ua[t] = a;
         ub[t] = a + u;
     }
-    constexpr unsigned FB = sizeof(frag_t);
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<frag_t*>(rf), (short)0, NT * KS * 64 * (int)FB, kBufferWord3);
-    const unsigned vlane = lane * FB;
-    frag_t rreg[C::RREG ? NT : 1][C::RREG ? KS : 1];
-    if constexpr (C::RREG) {
+    frag_t rreg[NT][KS];  // the reference fragments
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int s = 0; s < KS; ++s) rreg[t][s] = gload(rf + (t * KS + s) * 64 + lane);
-    }
+        for (int s = 0; s < KS; ++s) rreg[t][s] = gload(rf + (t * KS + s) * 64 + lane);
 
     // the rule's points and weights, once per workgroup
     __shared__ double sq[NQ * 4];
     for (int i = threadIdx.x; i < NQ * 4; i += blockDim.x) sq[i] = gload(A.qtab + i);
     __syncthreads();
 
-    // Persistent loop over 16-cell tiles, software-pipelined at degree 1:
+    // Persistent loop over 16-cell tiles, software-pipelined:
     // while tile i is contracted and stored, the vertices and field values of
     // tile i + 1 and the indices of tile i + 2 are in flight (issued before
     // this tile's stores, which share the in-order memory counter with them).
@@ -230,12 +225,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         const int64_t c = (t < A.ntiles ? t : tile) * 16 + col;
         return c < A.ncells ? c : A.ncells - 1;
     };
-    // degree 1 prefetches (short contraction, gather latency dominates); at
-    // degree 2 the contraction hides it and the registers go to occupancy
-    constexpr bool PIPE = P == 1;
     PrismIdx ix;
     PrismRaw<FD> raw;
-    if constexpr (PIPE) {
+    {
         prism_idx<FD>(A, clamp(tile), ix);
         prism_raw<FD>(A, clamp(tile), ix, raw);
         prism_idx<FD>(A, clamp(tile + stride), ix);
@@ -256,10 +248,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         constexpr bool FULL = decltype(full_tag)::value;
         const int64_t base = tile * 16;
         const bool valid = FULL || base + col < A.ncells;
-        if constexpr (!PIPE) {
-            prism_idx<FD>(A, clamp(tile), ix);
-            prism_raw<FD>(A, clamp(tile), ix, raw);
-        }
 
         // per-cell edge vectors of the map (bottom and top triangle edges from
         // vertex t0, vertical edges)
@@ -277,11 +265,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         double f[6];
 #pragma unroll
         for (int v = 0; v < 6; ++v) f[v] = FD > 0 ? raw.f[v] : 0.0;
-        if constexpr (PIPE) {
-            // next tile's values (indices loaded one tile ago), then the indices two ahead
-            prism_raw<FD>(A, clamp(tile + stride), ix, raw);
-            prism_idx<FD>(A, clamp(tile + 2 * stride), ix);
-        }
+        // next tile's values (indices loaded one tile ago), then the indices two ahead
+        prism_raw<FD>(A, clamp(tile + stride), ix, raw);
+        prism_idx<FD>(A, clamp(tile + 2 * stride), ix);
 
         // G entries of this lane's points q = grp, grp + 4, ...
         g_t* row = gt + col * ROW;
@@ -330,39 +316,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         acc_t acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = acc_t{0, 0, 0, 0};
-        if constexpr (C::RREG) {
-            // fragments in registers: straight-line code (constant indices);
-            // every G fragment is read from LDS before the first product, so
-            // the reads overlap one another instead of each MFMA pair waiting
-            // for its own read
-            frag_t afr[KS];
+        // straight-line code; every G fragment is read from LDS before the
+        // first product, so the reads overlap one another instead of each MFMA
+        // pair waiting for its own read
+        frag_t afr[KS];
 #pragma unroll
-            for (int s = 0; s < KS; ++s) afr[s] = load_afrag<PREC>(gt, ROW, lane, s);
+        for (int s = 0; s < KS; ++s) afr[s] = load_afrag<PREC>(gt, ROW, lane, s);
 #pragma unroll
-            for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(afr[s]));  // one wait for all reads
+        for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(afr[s]));  // one wait for all reads
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
+        for (int s = 0; s < KS; ++s)
 #pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = mfma<PREC>(afr[s], rreg[t][s], acc[t]);
-        } else {
-            // fragments through the caches as buffer loads (the lane's offset
-            // in one register, each n-tile's a constant), the next k-step's
-            // loads in flight during this k-step's products
-            frag_t b[NT];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) b[t] = buffer_frag<frag_t>(rsrc, vlane, t * KS * 64 * FB);
-#pragma unroll 1
-            for (int s = 0; s < KS; ++s) {
-                const frag_t a = load_afrag<PREC>(gt, ROW, lane, s);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = mfma<PREC>(a, b[t], acc[t]);
-                if (s + 1 < KS) {
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-                        b[t] = buffer_frag<frag_t>(rsrc, vlane + (s + 1) * 64 * FB, t * KS * 64 * FB);
-                }
-            }
-        }
+            for (int t = 0; t < NT; ++t) acc[t] = mfma<PREC>(afr[s], rreg[t][s], acc[t]);
         wave_sync();  // every G read is done: the staging area reuses the rows
 
         // two halves of 8 cells, each written to LDS in full (both triangles)
@@ -426,122 +391,338 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 }
 
 // ---------------------------------------------------------------- degrees 2, 3
-// At degree 3 (40 dofs, 820 unique entries in 52 n-tiles, 64 points, K = 448
-// for Helmholtz) one wave cannot hold the accumulators of all n-tiles, and 16
-// cells' matrices (205 KB in FP64) are larger than the LDS. A cell's matrix
-// written a few entries at a time over a long contraction leaves partial lines
-// that the L2 evicts before they are complete, so the matrices go out through
-// a staging area, a few whole cells at a time.
+// The basis, the rule and so the point products are tensor products of a
+// triangle and an interval factor. For interval dofs b, b' the block of the
+// element matrix over the triangle dofs is
+//     A[(a,b)][(a',b')] = sum_i sum_types (sum_j G_type(i, j) w_type,bb'(j)) R_type(i)[a][a'],
+// i the triangle points, j the interval points: the interval sum is taken
+// first (p + 1 multiply-adds per coefficient), and what is left is a
+// contraction over (i, type) with products of triangle functions alone. Types,
+// with the interval weight w: the pairs (0,0), (0,1), (1,1) of the triangle
+// directions (l_b l_b'), d_al phi_a phi_a' (l_b l'_b') and phi_a d_al phi_a'
+// (l'_b l_b') for al = 0, 1 (one type where b = b'), phi_a phi_a' (l'_b l'_b',
+// and l_b l_b' for the mass term). Only b <= b' is formed (the matrix is
+// symmetric) and, for b = b', a <= a'. Degree 2: 246 matrix products of 4 k's
+// per 16 cells, against 451 for the products over (point, term) with all
+// dof pairs; degree 3: 1,728 against 4,992.
 //
-// A workgroup takes two 16-cell tiles (32 cells): all its threads form the
-// 32 cells' G rows in LDS once (each thread one cell and a share of the
-// points), and each wave contracts both tiles' rows with its share of the
-// n-tiles, so that every R fragment loaded from L2 serves two products (one
-// fragment per product would ask the L2 for about 64 bytes per clock per CU
-// at the FP64 matrix-core rate, its whole bandwidth). Degree 3 runs eight
-// waves (6 or 7 of the 52 n-tiles each), degree 2 four (2 or 3 of 11). The
-// fragments of step s + 1 load during the products of step s. Then, in passes
-// of as many cells as fit in the G rows' LDS (four at degree 3, sixteen at
-// degree 2), the waves write their accumulators (both mirrored entries) into
-// that staging area, and the workgroup copies those cells out as contiguous
-// 16-byte stores.
-template <int FORM, int P, int FD, int PREC, int NQ>
-struct PrismBigCfg {
-    using C = PrismCfg<FORM, P, FD, PREC, NQ>;
-    static constexpr int CT = 2;  // 16-cell tiles per workgroup
-    // eight waves at degree 3 (52 n-tiles); four at degree 2 (11 n-tiles:
-    // three per wave, so that each G fragment read feeds six products)
-    static constexpr int WAVES = P >= 3 ? 8 : 4;
-    // n-tiles per wave. FP64/FP32: the first NT % WAVES waves take one more
-    // (waves w and w + 4 share a SIMD, so each SIMD gets an equal share when
-    // NT % WAVES <= 4), with no tile computed twice. BF16X3 (short products,
-    // where the per-tile branches cost more than they save): TCH tiles on
-    // every wave, tiles past NT repeating the last one, their products never
-    // stored.
-    static constexpr bool BAL = PREC != PREC_BF16X3;
-    static constexpr int TB = BAL ? C::NT / WAVES : (C::NT + WAVES - 1) / WAVES;
-    static constexpr int TR = BAL ? C::NT % WAVES : 0;
-    static constexpr int TCH = TB + (TR ? 1 : 0);
-    static constexpr int GT_BYTES = 16 * CT * C::ROW * (int)sizeof(typename C::g_t);
-    // cells per staging pass: the most (4, 8, 16 or 32) whose matrices fit in
-    // the G rows' LDS, at least four
-    static constexpr int CB = C::NN * (int)sizeof(typename C::out_t);
-    static constexpr int PC = 32 * CB <= GT_BYTES && CT == 2   ? 32
-                              : 16 * CB <= GT_BYTES             ? 16
-                              : 8 * CB <= GT_BYTES              ? 8
-                                                                : 4;
-    static constexpr int ST_BYTES = PC * CB;
-    static constexpr int LDS_BYTES = ((GT_BYTES > ST_BYTES ? GT_BYTES : ST_BYTES) + 15) / 16 * 16;
-    static_assert(LDS_BYTES + NQ * 32 <= 160 * 1024, "G rows, staging and the rule fit the LDS");
-    static_assert(C::NN * (int)sizeof(typename C::out_t) % 16 == 0, "cell matrices of whole 16-byte vectors");
+// A workgroup takes one 16-cell tile at degree 2, two at degree 3. Its threads,
+// one per cell and triangle point, form G at the points in LDS (FP64). Each
+// wave then owns pairs (b, b'): three waves with one pair b < b' and one pair
+// b = b' each at degree 2, eight at degree 3 (six with a pair b < b', two with
+// two pairs b = b'), which balances their products. Lane (cell, g) of a wave
+// forms the coefficients of its cell at the triangle points i = 4 ib + g, which
+// are its k's of the steps (ib, type): the G operand of a product never passes
+// through LDS. A ninth point (degree 2) is spread over the four lane groups
+// type by type. The R fragments, shared by every pair of a kind, are raw
+// buffer loads, one step ahead. Then, in passes of as many cells as the LDS
+// holds, the waves write their accumulators (both mirrored entries) into a
+// staging area over the G values, and the workgroup copies whole cells out as
+// 16-byte stores (a matrix written a few entries at a time leaves partial
+// lines that the L2 evicts).
+//
+// Degree 2 is bound by its instructions and the phases of a workgroup, so the
+// small tile (21 KB of LDS, many workgroups per CU) matters: two tiles per
+// workgroup ran 613 us in FP64 with three waves, 640 to 780 with six.
+// Diffusion, against the contraction over (point, term): 524,288 P2 prisms
+// FP64 656 -> 494 us, FP32 372 -> 302, BF16X3 262 -> 269; 65,536 P3 prisms
+// FP64 765 -> 367, FP32 415 -> 217, BF16X3 215 -> 176.
+// Workgroup barrier that orders LDS accesses only. Nothing passes between the
+// threads through global memory, and __syncthreads would also wait until
+// every outstanding store has reached memory and every prefetch has arrived
+// (two microseconds or more per staging pass).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <int FORM, int P, int FD, int PREC>
+struct PrismFacCfg {
+    using frag_t = typename PrecT<PREC>::frag;
+    using acc_t = typename PrecT<PREC>::acc;
+    using out_t = typename PrecT<PREC>::otype;
+    static constexpr bool BF = PREC == PREC_BF16X3;
+    static constexpr int M1 = P + 1;               // interval points, and dofs
+    static constexpr int NI = M1 * M1;             // triangle points
+    static constexpr int NQ = NI * M1;
+    static constexpr int NTRI = (P + 1) * (P + 2) / 2;
+    static constexpr int NS = NTRI * M1, NN = NS * NS;
+    static constexpr int JQ = prism_jq(FORM);      // G values per point
+    static constexpr int CELLG = (NQ * JQ) | 1;    // doubles of one cell
+    static constexpr int CT = P == 2 ? 1 : 2, CELLS = 16 * CT;  // tiles and cells of a workgroup
+    static constexpr int NOFF = M1 * (M1 - 1) / 2;
+    // kind 0: b < b', kind 1: b = b'
+    static constexpr int types(int kind) { return FORM == F_MASS ? 1 : (kind == 0 ? 8 : 6); }
+    static constexpr int entries(int kind) { return kind == 0 ? NTRI * NTRI : NTRI * (NTRI + 1) / 2; }
+    static constexpr int tiles(int kind) { return (entries(kind) + 15) / 16; }
+    static constexpr int FULLB = NI / 4, REM = NI % 4;
+    static_assert(REM <= 1, "one leftover point");
+    // k-steps (BF16X3: blocks of four points, eight type slots each, with a hi
+    // and a lo fragment)
+    static constexpr int steps(int kind) {
+        return BF ? 2 * ((NI + 3) / 4) : FULLB * types(kind) + (REM ? (types(kind) + 3) / 4 : 0);
+    }
+    static constexpr int frags(int kind) { return steps(kind) * tiles(kind) * 64; }
+    static constexpr int WAVES = P == 2 ? 3 : 8;
+    // degree 2: the workgroups of a CU hide each other's gathers; degree 3 has
+    // one per CU and prefetches
+    static constexpr bool PIPE = P == 3;
+    static constexpr int WPE = P == 2 ? 3 : 2;
+    // accumulator slots of a wave: degree 2 the tiles of its two pairs, degree
+    // 3 those of one pair b < b' or of two pairs b = b'
+    static constexpr int TW = P == 2 ? tiles(0) + tiles(1) : 2 * tiles(1);
+    static_assert(P == 2 || tiles(0) <= TW, "slots");
+    static constexpr int G_BYTES = CELLS * CELLG * 8;
+    static constexpr int CB = NN * (int)sizeof(out_t);
+    // accumulator elements (rows of a tile) and cells per staging pass
+    static constexpr int VP = (P == 2 ? 2 : 1) * (PREC == PREC_F64 ? 1 : 2), PC = 4 * CT * VP;
+    // staging rows and cells: degree 3 rows of 40 values would put the 16
+    // lanes of a mirrored column on two banks and the four cells of a lane
+    // group on the same ones (17 conflicting accesses per write on average;
+    // with 16 bytes more per row and per cell 3 to 5)
+    static constexpr int PADV = P == 3 ? 16 / (int)sizeof(out_t) : 0;
+    static constexpr int RS = NS + PADV, CS = NS * RS + PADV;
+    static constexpr int ST_BYTES = PC * CS * (int)sizeof(out_t);
+    static constexpr int LDS_BYTES = ((G_BYTES > ST_BYTES ? G_BYTES : ST_BYTES) + 15) / 16 * 16;
+    static_assert(LDS_BYTES + NQ * 32 <= 160 * 1024 && CB % 16 == 0, "LDS");
 };
 
-template <int FORM, int P, int FD, int PREC, int NQ>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_prism_big(PrismArgs A) {
-    using C = PrismCfg<FORM, P, FD, PREC, NQ>;
-    using B = PrismBigCfg<FORM, P, FD, PREC, NQ>;
-    using g_t = typename C::g_t;
+// Coefficients c[type] of a pair at triangle point i from the cell's G values.
+// w: the pair's interval weights [4][M1]: l l, l l', l' l, l' l'.
+template <int FORM, int P, int KIND>
+__device__ __forceinline__ void prism_coefs(const double* g, const double (&w)[4][P + 1], double* c) {
+    constexpr int M1 = P + 1, JQ = prism_jq(FORM), T = FORM == F_MASS ? 1 : (KIND == 0 ? 8 : 6);
+#pragma unroll
+    for (int t = 0; t < T; ++t) c[t] = 0.0;
+#pragma unroll
+    for (int j = 0; j < M1; ++j) {
+        const double* gj = g + j * JQ;
+        if constexpr (FORM == F_MASS) {
+            c[0] += w[0][j] * gj[0];
+        } else {
+            const double g02 = gj[2], g12 = gj[4];
+            c[0] += w[0][j] * gj[0];
+            c[1] += w[0][j] * gj[1];
+            c[2] += w[0][j] * gj[3];
+            c[3] += w[1][j] * g02;
+            c[4] += w[1][j] * g12;
+            if constexpr (KIND == 0) {
+                c[5] += w[2][j] * g02;
+                c[6] += w[2][j] * g12;
+            }
+            c[T - 1] += w[3][j] * gj[5];
+            if constexpr (FORM == F_HELM) c[T - 1] += w[0][j] * gj[6];
+        }
+    }
+}
+
+// Contraction of one pair (weights wt) of the given kind for the wave's tiles
+// (gt: their G values) into acc[c][S0 ...]. rf0: first fragment of the kind.
+template <int FORM, int P, int FD, int PREC, int KIND, int S0>
+__device__ __forceinline__ void prism_contract(const double* gt, const double* wt, __amdgpu_buffer_rsrc_t rsrc,
+                                               unsigned rf0, int lane,
+                                               typename PrecT<PREC>::acc (&acc)[PrismFacCfg<FORM, P, FD, PREC>::CT]
+                                                                              [PrismFacCfg<FORM, P, FD, PREC>::TW]) {
+    using C = PrismFacCfg<FORM, P, FD, PREC>;
+    using frag_t = typename C::frag_t;
+    constexpr int T = C::types(KIND), NT = C::tiles(KIND), M1 = C::M1, JQ = C::JQ, NC = C::CT;
+    constexpr unsigned FB = sizeof(frag_t);
+    const int g = lane >> 4;
+    const double* row[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) row[c] = gt + (16 * c + (lane & 15)) * C::CELLG;
+    double w[4][M1];  // wave-uniform
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int j = 0; j < M1; ++j) w[k][j] = cload(wt + k * M1 + j);
+    auto load_b = [&](frag_t* b, int s) {
+        const unsigned vo = (rf0 + (unsigned)(s * NT * 64) + lane) * FB;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) b[t] = buffer_frag<frag_t>(rsrc, vo, (unsigned)(t * 64) * FB);
+    };
+    if constexpr (C::BF) {
+        frag_t bh[NT], bl[NT];
+        load_b(bh, 0);
+        load_b(bl, 1);
+#pragma unroll 1
+        for (int ib = 0; ib < (C::NI + 3) / 4; ++ib) {
+            frag_t ah[NC], al[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const int i = 4 * ib + g;
+                double cf[T];
+                prism_coefs<FORM, P, KIND>(row[c] + (i < C::NI ? i : 0) * (M1 * JQ), w, cf);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const float x = t < T && (C::REM == 0 || i < C::NI) ? (float)cf[t < T ? t : 0] : 0.0f;
+                    ah[c][t] = (__bf16)x;
+                    al[c][t] = (__bf16)(x - (float)ah[c][t]);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    acc[c][S0 + t] = mfma<PREC>(ah[c], bh[t], acc[c][S0 + t]);
+                    acc[c][S0 + t] = mfma<PREC>(al[c], bh[t], acc[c][S0 + t]);
+                    acc[c][S0 + t] = mfma<PREC>(ah[c], bl[t], acc[c][S0 + t]);
+                    // the fourth product of the splits too: without it the
+                    // error against FP64 was 3.0e-6 (diffusion P3, norm), with
+                    // it 2.3e-6; over points and terms, without it, 2.6e-6
+                    acc[c][S0 + t] = mfma<PREC>(al[c], bl[t], acc[c][S0 + t]);
+                }
+            const int nb = ib + 1 < (C::NI + 3) / 4 ? ib + 1 : ib;
+            load_b(bh, 2 * nb);
+            load_b(bl, 2 * nb + 1);
+        }
+    } else {
+        constexpr int KS = C::steps(KIND);
+        frag_t b[2][NT];
+        load_b(b[0], 0);
+#pragma unroll 1
+        for (int ib = 0; ib < C::FULLB; ++ib) {
+            double cf[NC][T];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) prism_coefs<FORM, P, KIND>(row[c] + (4 * ib + g) * (M1 * JQ), w, cf[c]);
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int s = ib * T + t;
+                load_b(b[(t + 1) & 1], s + 1 < KS ? s + 1 : s);
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+                        acc[c][S0 + n] = mfma<PREC>((frag_t)cf[c][t], b[t & 1][n], acc[c][S0 + n]);
+            }
+            if constexpr (T % 2 == 1) {
+#pragma unroll
+                for (int n = 0; n < NT; ++n) b[0][n] = b[1][n];
+            }
+        }
+        if constexpr (C::REM > 0) {
+            // the leftover point: lane group g takes the types 4 t + g
+            double cf[NC][T];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) prism_coefs<FORM, P, KIND>(row[c] + (C::NI - 1) * (M1 * JQ), w, cf[c]);
+#pragma unroll
+            for (int t = 0; t < (T + 3) / 4; ++t) {
+                const int s = C::FULLB * T + t;
+                load_b(b[(t + 1) & 1], s + 1 < KS ? s + 1 : s);
+                frag_t x[NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    double v = cf[c][4 * t];
+#pragma unroll
+                    for (int k = 1; k < 4; ++k) {
+                        const double y = 4 * t + k < T ? cf[c][4 * t + k < T ? 4 * t + k : 0] : 0.0;
+                        v = g == k ? y : v;
+                    }
+                    x[c] = (frag_t)v;
+                }
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) acc[c][S0 + n] = mfma<PREC>(x[c], b[t & 1][n], acc[c][S0 + n]);
+            }
+        }
+    }
+}
+
+template <int FORM, int P, int FD, int PREC>
+__global__ __launch_bounds__((PrismFacCfg<FORM, P, FD, PREC>::WAVES * 64))
+__attribute__((amdgpu_waves_per_eu(PrismFacCfg<FORM, P, FD, PREC>::WPE))) void k_prism_fac(PrismArgs A) {
+    using C = PrismFacCfg<FORM, P, FD, PREC>;
     using frag_t = typename C::frag_t;
     using acc_t = typename C::acc_t;
     using out_t = typename C::out_t;
-    constexpr int NS = C::NS, NN = C::NN, NU = C::NU, NT = C::NT, KS = C::KS, JQ = C::JQ, KR = C::KR,
-                  ROW = C::ROW, TCH = B::TCH, CT = B::CT;
-    constexpr int CELLS = 16 * CT;  // cells per workgroup tile
+    constexpr int M1 = C::M1, NN = C::NN, NS = C::NS, NTRI = C::NTRI, NQ = C::NQ, JQ = C::JQ, TW = C::TW,
+                  CELLS = C::CELLS, NOFF = C::NOFF;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ double sq[NQ * 4];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    g_t* gt = reinterpret_cast<g_t*>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double* gt = reinterpret_cast<double*>(lds);
     out_t* st = reinterpret_cast<out_t*>(lds);
-    const frag_t* rf = reinterpret_cast<const frag_t*>(A.rfrag);
     out_t* out = reinterpret_cast<out_t*>(A.out);
-    // this wave's n-tiles t0 .. t0 + ntw - 1 (scalars)
-    const int wv = __builtin_amdgcn_readfirstlane(wave);
-    const int t0 = wv * B::TB + (wv < B::TR ? wv : B::TR);
-    const int ntw = B::TB + (wv < B::TR ? 1 : 0);
 
-    // staging offsets of this lane's unique entries u = 16 t + (lane & 15):
-    // (a, b), a <= b, row-major over the upper triangle (low half), and its
-    // mirror (b, a) (high half)
-    static_assert(NN <= 65536, "offsets in 16 bits");
-    unsigned off[TCH];
+    // staging offsets of this lane's entry in each accumulator slot: (row, col)
+    // in the low half, its mirror in the high half; all ones: no entry
+    static_assert(C::CS < 65535, "offsets in 16 bits");
+    unsigned off[TW];
 #pragma unroll
-    for (int i = 0; i < TCH; ++i) {
-        int u = 16 * (t0 + i) + (lane & 15), a = 0;
-        while (a < NS - 1 && u >= NS - a) {
-            u -= NS - a;
-            ++a;
+    for (int s = 0; s < TW; ++s) {
+        // slot -> pair (b, b2) and n-tile
+        int kind, pair, t;
+        if (P == 2) {
+            kind = s < C::tiles(0) ? 0 : 1;
+            pair = wave;
+            t = kind == 0 ? s : s - C::tiles(0);
+        } else {
+            kind = wave < NOFF ? 0 : 1;
+            pair = kind == 0 ? wave : 2 * (wave - NOFF) + s / C::tiles(1);
+            t = kind == 0 ? s : s % C::tiles(1);
         }
-        off[i] = (unsigned)(a * NS + a + u) | (unsigned)((a + u) * NS + a) << 16;
+        int b = pair, b2 = pair, a, a2, u = 16 * t + (lane & 15);
+        const bool ok = u < C::entries(kind);
+        if (kind == 0) {
+            b = 0;
+            int r = pair;
+            while (r >= M1 - 1 - b) {
+                r -= M1 - 1 - b;
+                ++b;
+            }
+            b2 = b + 1 + r;
+            a = u / NTRI;
+            a2 = u - a * NTRI;
+        } else {
+            a = 0;
+            while (a < NTRI - 1 && u >= NTRI - a) {
+                u -= NTRI - a;
+                ++a;
+            }
+            a2 = a + u;
+        }
+        const int rr = a * M1 + b, cc = a2 * M1 + b2;
+        off[s] = ok ? (unsigned)(rr * C::RS + cc) | (unsigned)(cc * C::RS + rr) << 16 : ~0u;
     }
     for (int i = tid; i < NQ * 4; i += blockDim.x) sq[i] = gload(A.qtab + i);
-    // the R fragments of this wave's n-tiles at k-step g, as buffer loads: the
-    // lane's offset in one register, each tile's offset a scalar
-    constexpr unsigned FB = sizeof(frag_t);
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<frag_t*>(rf), (short)0, NT * KS * 64 * (int)FB, kBufferWord3);
-    auto load_b = [&](frag_t* b, int g) {
-        const unsigned vo = ((unsigned)(t0 * KS + g) * 64 + lane) * FB;
-#pragma unroll
-        for (int i = 0; i < TCH; ++i)
-            if (i < ntw)
-                b[i] = buffer_frag<frag_t>(rsrc, vo, (unsigned)((B::BAL || t0 + i < NT ? i : NT - 1 - t0) * KS * 64) * FB);
-    };
+    // the interval weights follow the rule: [pairs b < b', then b = b'][4][M1]
+    const double* wtab = A.qtab + NQ * 4;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<frag_t*>(reinterpret_cast<const frag_t*>(A.rfrag)), (short)0,
+        (C::frags(0) + C::frags(1)) * (int)sizeof(frag_t), kBufferWord3);
 
     const int64_t ngroups = (A.ncells + CELLS - 1) / CELLS;
-    for (int64_t grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
+    const int r = tid % CELLS, pg = tid / CELLS;
+    static_assert(64 * C::WAVES / CELLS >= C::NI, "a thread per cell and triangle point");
+    auto cell_of = [&](int64_t grp) -> int64_t {
+        const int64_t c = grp * CELLS + r;
+        return c < A.ncells ? c : A.ncells - 1;
+    };
+    int64_t grp = blockIdx.x;
+    if (grp >= ngroups) return;  // the whole workgroup
+    // the next group's vertices and field values are in flight during the
+    // contraction, the indices of the one after it too
+    const int64_t GS = gridDim.x;
+    PrismIdx ix;
+    PrismRaw<FD> raw;
+    if constexpr (C::PIPE) {
+        prism_idx<FD>(A, cell_of(grp), ix);
+        prism_raw<FD>(A, cell_of(grp), ix, raw);
+        prism_idx<FD>(A, cell_of(grp + GS < ngroups ? grp + GS : grp), ix);
+    }
+    for (; grp < ngroups; grp += GS) {
         const int64_t base = grp * CELLS;
-        __syncthreads();  // the previous tile's staging reads are done (and sq is loaded)
-
-        // G rows: thread (cell r, point group pg) forms points pg, pg + 16, ...
+        if constexpr (!C::PIPE) {
+            prism_idx<FD>(A, cell_of(grp), ix);
+            prism_raw<FD>(A, cell_of(grp), ix, raw);
+        }
+        lds_barrier();  // the previous group's staging reads are done (and sq is loaded)
+        // G: thread (cell r, triangle point pg) forms the points of that vertical line
         {
-            const int r = tid % CELLS, pg = tid / CELLS;
-            constexpr int PG = 64 * B::WAVES / CELLS;  // point groups
             const bool valid = base + r < A.ncells;
-            const int64_t cell = valid ? base + r : A.ncells - 1;
-            PrismIdx ix;
-            PrismRaw<FD> raw;
-            prism_idx<FD>(A, cell, ix);
-            prism_raw<FD>(A, cell, ix, raw);
             double e[7][3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
@@ -553,132 +734,138 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
                 e[5][i] = raw.x[3][i] - raw.x[2][i];
                 e[6][i] = raw.x[5][i] - raw.x[4][i];
             }
-            g_t* row = gt + r * ROW;
-            // k padding past the G entries (the staging area overwrote it)
-            constexpr int KFILL = PREC == PREC_BF16X3 ? 3 * KR : KR;
-            for (int k = KFILL + pg; k < KS * kstep(PREC); k += PG) row[k] = g_t(0);
-#pragma unroll 1
-            for (int q = pg; q < NQ; q += PG) {
-                const double X = sq[4 * q], Y = sq[4 * q + 1], Z = sq[4 * q + 2], W = sq[4 * q + 3];
-                const double zb = 1.0 - Z, l0 = 1.0 - X - Y;
-                double J[3][3];
+            if (pg < C::NI) {
+                double* row = gt + r * C::CELLG + pg * (M1 * JQ);
+                const double X = sq[4 * pg * M1], Y = sq[4 * pg * M1 + 1], l0 = 1.0 - X - Y;
+                double J2[3];  // the vertical column does not depend on Z
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    J[i][0] = zb * e[0][i] + Z * e[1][i];
-                    J[i][1] = zb * e[2][i] + Z * e[3][i];
-                    J[i][2] = l0 * e[4][i] + X * e[5][i] + Y * e[6][i];
-                }
-                double K[3][3], adet;
-                prism_inverse(J, K, adet);
-                const double w = valid ? W * adet : 0.0;
-                int j = q * JQ;
-                if constexpr (FORM != F_MASS) {
-                    const double sc = FORM == F_DIFF ? w * A.kdt : w;
+                for (int i = 0; i < 3; ++i) J2[i] = l0 * e[4][i] + X * e[5][i] + Y * e[6][i];
 #pragma unroll
-                    for (int al = 0; al < 3; ++al)
+                for (int jz = 0; jz < M1; ++jz) {
+                    const double Z = sq[4 * (pg * M1 + jz) + 2], W = sq[4 * (pg * M1 + jz) + 3], zb = 1.0 - Z;
+                    double J[3][2];
 #pragma unroll
-                        for (int be = al; be < 3; ++be) {
-                            const double sv = K[al][0] * K[be][0] + K[al][1] * K[be][1] + K[al][2] * K[be][2];
-                            put_g<PREC, KR>(row, j++, sc * sv);
-                        }
-                }
-                if constexpr (FORM != F_DIFF) {
-                    double fq = 1.0;
-                    if constexpr (FD > 0)
-                        fq = (l0 * raw.f[0] + X * raw.f[2] + Y * raw.f[4]) * zb +
-                             (l0 * raw.f[1] + X * raw.f[3] + Y * raw.f[5]) * Z;
-                    put_g<PREC, KR>(row, j, w * fq);
+                    for (int i = 0; i < 3; ++i) {
+                        J[i][0] = zb * e[0][i] + Z * e[1][i];
+                        J[i][1] = zb * e[2][i] + Z * e[3][i];
+                    }
+                    // rows of det J K (cofactors)
+                    const double c[3][3] = {{J[1][1] * J2[2] - J2[1] * J[2][1], J2[0] * J[2][1] - J[0][1] * J2[2],
+                                             J[0][1] * J2[1] - J2[0] * J[1][1]},
+                                            {J2[1] * J[2][0] - J[1][0] * J2[2], J[0][0] * J2[2] - J2[0] * J[2][0],
+                                             J2[0] * J[1][0] - J[0][0] * J2[1]},
+                                            {J[1][0] * J[2][1] - J[1][1] * J[2][0], J[0][1] * J[2][0] - J[0][0] * J[2][1],
+                                             J[0][0] * J[1][1] - J[0][1] * J[1][0]}};
+                    const double det = J[0][0] * c[0][0] + J[1][0] * c[0][1] + J[2][0] * c[0][2], adet = fabs(det);
+                    double* pq = row + jz * JQ;
+                    int t = 0;
+                    if constexpr (FORM != F_MASS) {
+                        // W |det J| K K^T = (W / |det J|) c c^T
+                        const double w = valid ? (FORM == F_DIFF ? W * A.kdt : W) / adet : 0.0;
+#pragma unroll
+                        for (int al = 0; al < 3; ++al)
+#pragma unroll
+                            for (int be = al; be < 3; ++be)
+                                pq[t++] = w * (c[al][0] * c[be][0] + c[al][1] * c[be][1] + c[al][2] * c[be][2]);
+                    }
+                    if constexpr (FORM != F_DIFF) {
+                        double fq = valid ? W * adet : 0.0;
+                        if constexpr (FD > 0)
+                            fq *= (l0 * raw.f[0] + X * raw.f[2] + Y * raw.f[4]) * zb +
+                                  (l0 * raw.f[1] + X * raw.f[3] + Y * raw.f[5]) * Z;
+                        pq[t] = fq;
+                    }
                 }
             }
         }
-        frag_t b[TCH];
-        load_b(b, 0);
-        __syncthreads();
+        if constexpr (C::PIPE) {
+            const int64_t n1 = grp + GS < ngroups ? grp + GS : grp;
+            prism_raw<FD>(A, cell_of(n1), ix, raw);
+            prism_idx<FD>(A, cell_of(n1 + GS < ngroups ? n1 + GS : n1), ix);
+        }
+        lds_barrier();
 
-        // contraction of the two tiles' G rows with this wave's n-tiles (the G
-        // fragments of step s + 1 are read during the products of step s)
-        acc_t acc[CT][TCH];
+        acc_t acc[C::CT][TW];
 #pragma unroll
-        for (int c = 0; c < CT; ++c)
+        for (int c = 0; c < C::CT; ++c)
 #pragma unroll
-            for (int i = 0; i < TCH; ++i) acc[c][i] = acc_t{0, 0, 0, 0};
-        frag_t a[CT];
-#pragma unroll
-        for (int c = 0; c < CT; ++c) a[c] = load_afrag<PREC>(gt + 16 * c * ROW, ROW, lane, 0);
-        // one k-step: the products of step s with R fragments bc, the G
-        // fragments of step s + 1 read meanwhile; R fragments of step s + 1
-        // into bn (issued before the products when bn is a second buffer,
-        // after them when it is bc itself)
-        auto step = [&](int s, frag_t* bc, frag_t* bn) {
-            if (bn != bc && s + 1 < KS) load_b(bn, s + 1);
-            frag_t an[CT];
-#pragma unroll
-            for (int c = 0; c < CT; ++c) an[c] = load_afrag<PREC>(gt + 16 * c * ROW, ROW, lane, s + 1 < KS ? s + 1 : s);
-#pragma unroll
-            for (int i = 0; i < TCH; ++i)
-                if (i < ntw) {
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) acc[c][i] = mfma<PREC>(a[c], bc[i], acc[c][i]);
-                }
-            if (bn == bc && s + 1 < KS) load_b(bc, s + 1);
-#pragma unroll
-            for (int c = 0; c < CT; ++c) a[c] = an[c];
-        };
-        if constexpr (B::BAL) {
-            // FP64/FP32: two R buffers (BF16X3's short products were slower so)
-            frag_t b1[TCH];
-#pragma unroll 1
-            for (int s = 0; s < KS; s += 2) {
-                step(s, b, b1);
-                if (s + 1 < KS) step(s + 1, b1, b);
-            }
+            for (int i = 0; i < TW; ++i) acc[c][i] = acc_t{0, 0, 0, 0};
+        const double* wd = wtab + NOFF * 4 * M1;  // weights of the pairs b = b'
+        if constexpr (P == 2) {
+            prism_contract<FORM, P, FD, PREC, 0, 0>(gt, wtab + wave * 4 * M1, rsrc, 0, lane, acc);
+            prism_contract<FORM, P, FD, PREC, 1, C::tiles(0)>(gt, wd + wave * 4 * M1, rsrc, C::frags(0), lane, acc);
+        } else if (wave < NOFF) {
+            prism_contract<FORM, P, FD, PREC, 0, 0>(gt, wtab + wave * 4 * M1, rsrc, 0, lane, acc);
         } else {
-#pragma unroll 1
-            for (int s = 0; s < KS; ++s) step(s, b, b);
+            const double* w2 = wd + 2 * (wave - NOFF) * 4 * M1;
+            prism_contract<FORM, P, FD, PREC, 1, 0>(gt, w2, rsrc, C::frags(0), lane, acc);
+            prism_contract<FORM, P, FD, PREC, 1, TW - C::tiles(1)>(gt, w2 + 4 * M1, rsrc, C::frags(0), lane, acc);
         }
 
-        // 4 CT / NVP passes. Pass p holds the NVP (tile c, accumulator element
-        // v) pairs j = p NVP .. p NVP + NVP - 1, c = j / 4, v = j % 4; staging
-        // slot 4 jj + lane / 16 is the cell of pair jj held by lane group
-        // lane / 16.
-        constexpr int NVP = B::PC / 4;
+        // 4 / VP passes: pass p holds the accumulator elements v = p VP + vv of
+        // every tile c, the cells acc_row(16 g, v) of lane groups g, in slots
+        // of increasing cell
+        constexpr int VP = C::VP;
         constexpr int NV1 = NN * (int)sizeof(out_t) / 16;  // 16-byte vectors per cell
         const u32x4p* s4 = reinterpret_cast<const u32x4p*>(st);
 #pragma unroll
-        for (int p = 0; p < 4 * CT / NVP; ++p) {
-            __syncthreads();  // G reads (first pass) or the previous pass's copies are done
+        for (int p = 0; p < 4 / VP; ++p) {
+            lds_barrier();  // G reads (first pass) or the previous pass's copies are done
 #pragma unroll
-            for (int jj = 0; jj < NVP; ++jj) {
-                const int c = (p * NVP + jj) / 4, v = (p * NVP + jj) % 4;
+            for (int i = 0; i < TW; ++i) {
+                if (off[i] == ~0u) continue;
 #pragma unroll
-                for (int i = 0; i < TCH; ++i) {
-                    if (i >= ntw || 16 * (t0 + i) + (lane & 15) >= NU) continue;
-                    const out_t x = (out_t)acc[c][i][v];
-                    st[(4 * jj + (lane >> 4)) * NN + (off[i] & 0xffff)] = x;
-                    st[(4 * jj + (lane >> 4)) * NN + (off[i] >> 16)] = x;
-                }
+                for (int c = 0; c < C::CT; ++c)
+#pragma unroll
+                    for (int vv = 0; vv < VP; ++vv) {
+                        const out_t x = (out_t)acc[c][i][p * VP + vv];
+                        out_t* sl = st + (c * 4 * VP + (PREC == PREC_F64 ? vv * 4 + (lane >> 4) : (lane >> 4) * VP + vv)) * C::CS;
+                        sl[off[i] & 0xffff] = x;
+                        sl[off[i] >> 16] = x;
+                    }
             }
-            __syncthreads();
-            if constexpr (NVP >= 4) {
-                // whole tiles: the pass's cells are contiguous, copied in
-                // memory order (lines shared by neighbouring cells are then
-                // written together); cell r of a tile sits in the slot of
-                // its (lane group, v)
-                const int64_t c0 = base + 16 * (p * NVP / 4);
-                for (int k = tid; k < B::PC * NV1; k += blockDim.x) {
-                    const int lc = k / NV1, r = lc % 16;
-                    const int g = PREC == PREC_F64 ? r % 4 : r / 4, v = PREC == PREC_F64 ? r / 4 : r % 4;
-                    const int slot = 4 * (4 * (lc / 16) + v) + g;
-                    if (c0 + lc < A.ncells)
-                        gstore_nt(reinterpret_cast<u32x4p*>(out + (c0 + lc) * NN) + (k - lc * NV1),
-                                  s4[slot * NV1 + (k - lc * NV1)]);
+            lds_barrier();
+            // copy out the pass's cells in memory order (consecutive ones share
+            // lines), four vectors a thread at a time so that their LDS reads
+            // overlap
+            constexpr int NVEC = C::PC * NV1, TH = 64 * C::WAVES;
+            if constexpr (C::PADV == 0 && C::CT == 1) {
+                // one range in LDS and in memory
+                static_assert(PREC == PREC_F64 || VP == 4, "consecutive cells");
+                const int64_t c0 = base + 4 * VP * p;
+                const int nv = A.ncells - c0 < 4 * VP ? (int)(A.ncells - c0) * NV1 : NVEC;
+                u32x4p* o4 = reinterpret_cast<u32x4p*>(out + c0 * NN);
+#pragma unroll
+                for (int k0 = 0; k0 < NVEC; k0 += 4 * TH) {
+                    u32x4p x[4];
+#pragma unroll
+                    for (int n = 0; n < 4; ++n)
+                        if (k0 + n * TH < NVEC) x[n] = s4[k0 + n * TH + tid < NVEC ? k0 + n * TH + tid : tid];
+#pragma unroll
+                    for (int n = 0; n < 4; ++n)
+                        if (k0 + n * TH < NVEC && k0 + n * TH + tid < nv) gstore_nt(&o4[k0 + n * TH + tid], x[n]);
                 }
             } else {
-                for (int k = tid; k < B::PC * NV1; k += blockDim.x) {
-                    const int slot = k / NV1, j = p * NVP + slot / 4;
-                    const int64_t cl = base + 16 * (j / 4) + acc_row<PREC>(16 * (slot % 4), j % 4);
-                    if (cl < A.ncells)
-                        gstore_nt(reinterpret_cast<u32x4p*>(out + cl * NN) + (k - slot * NV1), s4[k]);
+#pragma unroll 1
+                for (int k0 = tid; k0 < NVEC; k0 += 4 * TH) {
+                    u32x4p x[4];
+                    int64_t cl[4];
+                    int at[4];
+#pragma unroll
+                    for (int n = 0; n < 4; ++n) {
+                        const int k = k0 + n * TH < NVEC ? k0 + n * TH : k0;
+                        const int slot = k / NV1, in = k - slot * NV1;  // cell of the pass, vector of its matrix
+                        const int c = slot / (4 * VP), m = slot % (4 * VP);
+                        const int g = PREC == PREC_F64 ? m % 4 : m / VP, vv = PREC == PREC_F64 ? m / 4 : m % VP;
+                        cl[n] = k0 + n * TH < NVEC ? base + 16 * c + acc_row<PREC>(16 * g, p * VP + vv) : A.ncells;
+                        at[n] = in;
+                        constexpr int RV = NS * (int)sizeof(out_t) / 16, PV = C::PADV > 0 ? 1 : 0;  // vectors of a row
+                        const int row = in / RV;
+                        x[n] = s4[slot * (C::CS * (int)sizeof(out_t) / 16) + row * (RV + PV) + (in - row * RV)];
+                    }
+#pragma unroll
+                    for (int n = 0; n < 4; ++n)
+                        if (cl[n] < A.ncells) gstore_nt(reinterpret_cast<u32x4p*>(out + cl[n] * NN) + at[n], x[n]);
                 }
             }
         }
@@ -690,6 +877,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
 namespace {
 
 using ld = long double;
+
+uint16_t bf16_bits_host(float x) {
+    uint32_t u;
+    std::memcpy(&u, &x, 4);
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return (uint16_t)(u >> 16);
+}
+float bf16_float_host(uint16_t h) {
+    const uint32_t u = ((uint32_t)h) << 16;
+    float f;
+    std::memcpy(&f, &u, 4);
+    return f;
+}
 
 // Reference products per point (no weights; the weights are in G), in the
 // device's column order k = q JQ + j.
@@ -728,6 +928,102 @@ bool prism_reference(int form, int p, int quad, RefTensor& R, std::vector<double
     return true;
 }
 
+// Degrees 2 and 3: fragments of the triangle products of both kinds of pairs
+// in the k order of k_prism_fac, and the rule followed by the interval weights.
+template <typename C>
+void prism_fac_pack(const std::vector<ld> (&R)[2], int prec, std::vector<char>& frag) {
+    // R[kind]: [type][triangle point][entry]
+    for (int kind = 0; kind < 2; ++kind) {
+        const int T = C::types(kind), NE = C::entries(kind), NT = C::tiles(kind);
+        auto val = [&](int type, int i, int u) -> double {
+            return type < T && i < C::NI && u < NE ? (double)R[kind][((size_t)type * C::NI + i) * NE + u] : 0.0;
+        };
+        auto put = [&](const void* p, size_t n) { frag.insert(frag.end(), (const char*)p, (const char*)p + n); };
+        for (int s = 0; s < C::steps(kind); ++s)
+            for (int t = 0; t < NT; ++t)
+                for (int l = 0; l < 64; ++l) {
+                    const int g = l / 16, u = 16 * t + l % 16;
+                    if (C::BF) {
+                        // block s / 2 of four points, slot = type; hi, then lo
+                        for (int k = 0; k < 8; ++k) {
+                            const float x = (float)val(k, 4 * (s / 2) + g, u);
+                            const uint16_t hi = bf16_bits_host(x);
+                            const uint16_t h = s % 2 == 0 ? hi : bf16_bits_host(x - bf16_float_host(hi));
+                            put(&h, 2);
+                        }
+                    } else {
+                        const bool full = s < C::FULLB * T;
+                        const int type = full ? s % T : 4 * (s - C::FULLB * T) + g;
+                        const int i = full ? 4 * (s / T) + g : C::NI - 1;
+                        const double x = val(type, i, u);
+                        const float f = (float)x;
+                        if (prec == COFFEE_FP64) put(&x, 8);
+                        else put(&f, 4);
+                    }
+                }
+    }
+}
+
+template <int FORM, int P, int PREC>
+void prism_fac_pack_prec(const std::vector<ld> (&R)[2], std::vector<char>& frag) {
+    prism_fac_pack<dev::PrismFacCfg<FORM, P, 0, PREC>>(R, PREC, frag);
+}
+
+template <int FORM, int P>
+bool prism_fac_tables(int quad, int prec, std::vector<char>& frag, std::vector<double>& qtab) {
+    Tables tri;
+    std::vector<ld> l, dl;
+    constexpr int M1 = P + 1;
+    PrismTables pt;
+    if (!tri.init(2, P, quad) || tri.nq != M1 * M1 || !interval_tables(P, M1, l, dl) || !pt.init(P, quad)) return false;
+    const int n = tri.n, ni = tri.nq;
+    std::vector<ld> R[2];
+    for (int kind = 0; kind < 2; ++kind) {
+        const int T = FORM == dev::F_MASS ? 1 : (kind == 0 ? 8 : 6);
+        for (int type = 0; type < T; ++type)
+            for (int i = 0; i < ni; ++i)
+                for (int a = 0; a < n; ++a)
+                    for (int b = kind == 0 ? 0 : a; b < n; ++b) {
+                        auto ph = [&](int x) { return tri.phi[(size_t)i * n + x]; };
+                        auto d = [&](int al, int x) { return tri.dphi[((size_t)al * ni + i) * n + x]; };
+                        ld v;
+                        if (FORM == dev::F_MASS || type == T - 1) v = ph(a) * ph(b);
+                        else if (type == 0) v = d(0, a) * d(0, b);
+                        else if (type == 1) v = d(0, a) * d(1, b) + d(1, a) * d(0, b);
+                        else if (type == 2) v = d(1, a) * d(1, b);
+                        else if (kind == 1) v = d(type - 3, a) * ph(b) + ph(a) * d(type - 3, b);
+                        else if (type <= 4) v = d(type - 3, a) * ph(b);
+                        else v = ph(a) * d(type - 5, b);
+                        R[kind].push_back(v);
+                    }
+    }
+    frag.clear();
+    if (prec == COFFEE_FP64) prism_fac_pack_prec<FORM, P, dev::PREC_F64>(R, frag);
+    else if (prec == COFFEE_FP32) prism_fac_pack_prec<FORM, P, dev::PREC_F32>(R, frag);
+    else prism_fac_pack_prec<FORM, P, dev::PREC_BF16X3>(R, frag);
+    qtab.clear();
+    for (int k = 0; k < pt.nq; ++k) {
+        for (int i = 0; i < 3; ++i) qtab.push_back((double)pt.X[3 * k + i]);
+        qtab.push_back((double)pt.W[k]);
+    }
+    auto weights = [&](int b, int b2) {
+        for (int k = 0; k < 4; ++k)
+            for (int j = 0; j < M1; ++j)
+                qtab.push_back((double)((k & 2 ? dl : l)[j * M1 + b] * (k & 1 ? dl : l)[j * M1 + b2]));
+    };
+    for (int b = 0; b < M1; ++b)
+        for (int b2 = b + 1; b2 < M1; ++b2) weights(b, b2);
+    for (int b = 0; b < M1; ++b) weights(b, b);
+    return true;
+}
+
+template <int P>
+bool prism_fac_tables_form(int form, int quad, int prec, std::vector<char>& frag, std::vector<double>& qtab) {
+    if (form == COFFEE_MASS) return prism_fac_tables<dev::F_MASS, P>(quad, prec, frag, qtab);
+    if (form == COFFEE_HELMHOLTZ) return prism_fac_tables<dev::F_HELM, P>(quad, prec, frag, qtab);
+    return prism_fac_tables<dev::F_DIFF, P>(quad, prec, frag, qtab);
+}
+
 struct PrismTable {
     void* frag = nullptr;
     double* qtab = nullptr;
@@ -744,10 +1040,16 @@ coffee_status prism_table(int dev, int form, int p, int quad, int prec, PrismTab
         *out = it->second;
         return COFFEE_OK;
     }
-    RefTensor R;
     std::vector<double> qtab;
-    if (!prism_reference(form, p, quad, R, qtab)) return COFFEE_E_INVALID_ARG;
-    const std::vector<char> frag = pack_fragments(R, prec, true, 0);
+    std::vector<char> frag;
+    if (p == 1) {
+        RefTensor R;
+        if (!prism_reference(form, p, quad, R, qtab)) return COFFEE_E_INVALID_ARG;
+        frag = pack_fragments(R, prec, true, 0);
+    } else if (!(p == 2 ? prism_fac_tables_form<2>(form, quad, prec, frag, qtab)
+                        : prism_fac_tables_form<3>(form, quad, prec, frag, qtab))) {
+        return COFFEE_E_INVALID_ARG;
+    }
     PrismTable t;
     if (hipMalloc(&t.frag, frag.size()) != hipSuccess) return COFFEE_E_NOMEM;
     if (hipMalloc((void**)&t.qtab, qtab.size() * sizeof(double)) != hipSuccess) {
@@ -781,28 +1083,31 @@ hipError_t launch_prism(const dev::PrismArgs& a, hipStream_t s, int dev_id) {
     return hipGetLastError();
 }
 
-template <int FORM, int P, int FD, int PREC, int NQ>
-hipError_t launch_prism_big(const dev::PrismArgs& a, hipStream_t s, int dev_id) {
-    using B = dev::PrismBigCfg<FORM, P, FD, PREC, NQ>;
-    const void* kern = reinterpret_cast<const void*>(&dev::k_prism_big<FORM, P, FD, PREC, NQ>);
+template <int FORM, int P, int FD, int PREC>
+hipError_t launch_prism_fac(const dev::PrismArgs& a, hipStream_t s, int dev_id) {
+    using C = dev::PrismFacCfg<FORM, P, FD, PREC>;
+    const void* kern = reinterpret_cast<const void*>(&dev::k_prism_fac<FORM, P, FD, PREC>);
     static const hipError_t attr =
-        hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, B::LDS_BYTES);
+        hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (attr != hipSuccess) return attr;
-    const int64_t wgs_needed = (a.ncells + 16 * B::CT - 1) / (16 * B::CT);  // one tile group per workgroup at a time
+    const int64_t wgs_needed = (a.ncells + C::CELLS - 1) / C::CELLS;  // one cell group per workgroup at a time
     int tuned_variant = 0;
     const int tuned = tuned_linear(FORM, COFFEE_PRISM, P, FD, PREC, &tuned_variant);
-    const int grid = grid_for(dev_id, kern, B::WAVES * 64, B::LDS_BYTES, wgs_needed, tuned > 0 ? tuned : 1);
-    hipLaunchKernelGGL((dev::k_prism_big<FORM, P, FD, PREC, NQ>), dim3(grid), dim3(B::WAVES * 64), B::LDS_BYTES, s,
-                       a);
+    // degree 2: short-lived workgroups (16 grids of the resident set) ran 494
+    // us against 522 for one persistent set (FP64 diffusion, 524,288 cells);
+    // degree 3, which prefetches: 385 against 367 (65,536 cells)
+    const int grid = grid_for(dev_id, kern, C::WAVES * 64, C::LDS_BYTES, wgs_needed,
+                              tuned > 0 ? tuned : (P == 2 ? 16 : 1));
+    hipLaunchKernelGGL((dev::k_prism_fac<FORM, P, FD, PREC>), dim3(grid), dim3(C::WAVES * 64), C::LDS_BYTES, s, a);
     return hipGetLastError();
 }
 
 template <int FORM, int P, int FD, int NQ>
 hipError_t launch_prism_prec(int prec, const dev::PrismArgs& a, hipStream_t s, int dev_id) {
     if constexpr (P >= 2) {
-        if (prec == COFFEE_FP64) return launch_prism_big<FORM, P, FD, dev::PREC_F64, NQ>(a, s, dev_id);
-        if (prec == COFFEE_FP32) return launch_prism_big<FORM, P, FD, dev::PREC_F32, NQ>(a, s, dev_id);
-        return launch_prism_big<FORM, P, FD, dev::PREC_BF16X3, NQ>(a, s, dev_id);
+        if (prec == COFFEE_FP64) return launch_prism_fac<FORM, P, FD, dev::PREC_F64>(a, s, dev_id);
+        if (prec == COFFEE_FP32) return launch_prism_fac<FORM, P, FD, dev::PREC_F32>(a, s, dev_id);
+        return launch_prism_fac<FORM, P, FD, dev::PREC_BF16X3>(a, s, dev_id);
     } else {
         if (prec == COFFEE_FP64) return launch_prism<FORM, P, FD, dev::PREC_F64, NQ>(a, s, dev_id);
         if (prec == COFFEE_FP32) return launch_prism<FORM, P, FD, dev::PREC_F32, NQ>(a, s, dev_id);

@@ -49,6 +49,9 @@ struct PrismTables {
     std::vector<long double> X, W, phi, dphi;  // [nq][3], [nq], [nq][n], [3][nq][n]
     bool init(int p, int quad);
 };
+// Degree-p basis on [0,1] (prism dof order) and its derivative at the m
+// Gauss-Legendre points: [m][p + 1].
+bool interval_tables(int p, int m, std::vector<long double>& l, std::vector<long double>& dl);
 int prism_rule_size(int quad);  // -1 if the rule does not exist
 int n_prism(int p);
 

@@ -339,6 +339,23 @@ static bool interval_basis(int p, ld (*coef)[kMaxP + 1]) {
     return true;
 }
 
+bool interval_tables(int p, int m, std::vector<ld>& l, std::vector<ld>& dl) {
+    ld z[16], wz[16], coef[kMaxP + 1][kMaxP + 1];
+    if (p < 0 || p > kMaxP || !gauss_jacobi01(m, 0, z, wz) || !interval_basis(p, coef)) return false;
+    l.assign((size_t)m * (p + 1), 0.0L);
+    dl.assign((size_t)m * (p + 1), 0.0L);
+    for (int j = 0; j < m; ++j)
+        for (int b = 0; b <= p; ++b) {
+            ld pw = 1.0L;
+            for (int e = 0; e <= p; ++e) {
+                l[j * (p + 1) + b] += coef[e][b] * pw;
+                if (e + 1 <= p) dl[j * (p + 1) + b] += coef[e + 1][b] * (e + 1) * pw;
+                pw *= z[j];
+            }
+        }
+    return true;
+}
+
 bool PrismTables::init(int p_, int quad) {
     p = p_;
     Basis tb;

@@ -206,3 +206,26 @@ def test_diffusion_adjoint_vs_oracle(cf, oracle, d, p, deterministic):
     S = float(cv.sum())
     assert abs(S - S_ref) <= 1e-11 * abs(S_ref)
     assert rel(gc.cpu().numpy(), gc_ref) < 1e-10
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("form,p,field", [("diffusion", 2, None), ("helmholtz", 2, "map"), ("mass", 2, "cellmajor"),
+                                          ("diffusion", 3, None), ("helmholtz", 3, "cellmajor"), ("mass", 3, None)])
+def test_prism_factored_ragged_counts(cf, oracle, form, p, field, prec):
+    """Degrees 2 and 3 (contraction factored over triangle and interval) at counts around the 16- and 32-cell
+    workgroup tiles and the staging passes of 4, 8 and 16 cells, with the field through a dof map and cell-major."""
+    from gpu_util import TOL, assemble_gpu, cell_rel_err
+    rng = np.random.default_rng(700 + p)
+    mesh = I.make_prism_mesh(4, 0.12, rng)
+    vals = rng.uniform(0.5, 1.5, (mesh.nvert, 1))
+    cst = [1.3, 0.4] if form == "diffusion" else []
+    for count in (1, 4, 7, 15, 16, 17, 31, 33, 65):
+        sub = I.Mesh(3, 4, mesh.coords, np.ascontiguousarray(mesh.cells[:count]))
+        fields = []
+        if field == "map":
+            fields = [I.Field(vals, sub.cells, 1, 1)]
+        elif field == "cellmajor":
+            fields = [I.Field(np.ascontiguousarray(vals[sub.cells]), None, 1, 1)]
+        ref = oracle.assemble(form, sub, p, fields=fields, constants=cst)
+        got = assemble_gpu(form, sub, p, fields, constants=cst, precision=prec).cpu().numpy()
+        assert cell_rel_err(got, ref) < TOL[prec], count
