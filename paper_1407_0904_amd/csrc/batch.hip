@@ -8,8 +8,8 @@
 //    of the workspace (ranks inside a slice from wave ballots), so that the
 //    entries of a bin keep their input order.
 // 2. One persistent kernel: every wave takes tasks (task_cells consecutive
-//    binned entries of one bin) from a single atomic queue that lists the bins
-//    in segment order, and runs the symmetric-form engine of that bin's
+//    binned entries of one bin, fewer where the batch is small) from a single
+//    atomic queue that lists the bins in segment order, and runs the symmetric-form engine of that bin's
 //    (form, shape, degree) on them 64 entries at a time, software-pipelined
 //    three deep inside the task (while group g is contracted and stored, the
 //    coordinates and coefficient dofs of group g+1, the vertex indices of
@@ -617,44 +617,39 @@ __device__ inline void batch_dispatch_v(const BatchArgs* A, const BinDesc* bd, i
 // bin, or 64 padded degree-1 tensors).
 template <int PREC>
 __global__ __launch_bounds__(256) void k_batch(const BatchArgs* __restrict__ Ap, int stage_elems) {
-    const BatchArgs& A = *Ap;
+    const BatchArgs* A = uniform_ptr(Ap);
     using out_t = typename PrecT<PREC>::otype;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned per_wave = WaveLds<PREC>::GT_BYTES + kSoffs * sizeof(int64_t) + (unsigned)stage_elems * sizeof(out_t);
     const unsigned wave_off = wave * per_wave;
-    // tasks per bin from the device counts
-    int64_t tstart[kMaxBins + 1];
-    tstart[0] = 0;
-#pragma unroll
-    for (int b = 0; b < kMaxBins; ++b) {
-        const int64_t c = b < A.nbins ? (int64_t)A.counts[b] : 0;
-        const int tc = b < A.nbins ? A.bins[b].task_cells : 64;
-        tstart[b + 1] = tstart[b] + (c + tc - 1) / tc;
-    }
-    const int64_t total = tstart[kMaxBins];
+    const int nbins = cload(&A->nbins);
     for (;;) {
-        unsigned long long t = 0;
-        if (lane == 0) t = atomicAdd(A.queue, 1ull);
-        t = (unsigned long long)uniform_i64((int64_t)__shfl(t, 0));
-        if ((int64_t)t >= total) break;
-        int b = 0;
-        int64_t tb = 0;
-#pragma unroll
-        for (int k = 1; k < kMaxBins; ++k)
-            if ((int64_t)t >= tstart[k]) {
+        unsigned long long q = 0;
+        if (lane == 0) q = atomicAdd(cload(&A->queue), 1ull);
+        int64_t t = uniform_i64((int64_t)q);
+        // the bin of task t and the task's number in it, from the device counts
+        int b = -1;
+        for (int k = 0; k < nbins; ++k) {
+            const int tc = cload(&A->bins[k].task_cells);
+            const int64_t nt = ((int64_t)cload(cload(&A->counts) + k) + tc - 1) / tc;
+            if (t < nt) {
                 b = k;
-                tb = tstart[k];
+                break;
             }
-        const BinDesc* bd = &Ap->bins[b];
-        const int tc = bd->task_cells, type = bd->type, variant = bd->variant;
-        const bool mapped = bd->f0.map != nullptr;
-        const int64_t local = ((int64_t)t - tb) * tc;
-        const int64_t cnt = (int64_t)A.counts[b];
+            t -= nt;
+        }
+        if (b < 0) break;
+        const BinDesc* bd = &A->bins[b];
+        const int tc = cload(&bd->task_cells), type = cload(&bd->type), variant = cload(&bd->variant);
+        const bool mapped = cload(&bd->f0.map) != nullptr;
+        const int64_t cnt = (int64_t)cload(cload(&A->counts) + b);
+        const int64_t local = t * tc;
         const int n = (int)(cnt - local < tc ? cnt - local : tc);
-        const int64_t first = (int64_t)A.offs[b] + local;
-        if (variant == 2) batch_dispatch_v<PREC, 2>(Ap, bd, type, mapped, b, first, n, lane, wave_off);
-        else if (variant == 0) batch_dispatch_v<PREC, 0>(Ap, bd, type, mapped, b, first, n, lane, wave_off);
-        else batch_dispatch_v<PREC, 1>(Ap, bd, type, mapped, b, first, n, lane, wave_off);
+        const int64_t first = (int64_t)cload(cload(&A->offs) + b) + local;
+        if (variant == 2) batch_dispatch_v<PREC, 2>(A, bd, type, mapped, b, first, n, lane, wave_off);
+        else if (variant == 0) batch_dispatch_v<PREC, 0>(A, bd, type, mapped, b, first, n, lane, wave_off);
+        else batch_dispatch_v<PREC, 1>(A, bd, type, mapped, b, first, n, lane, wave_off);
     }
 }
 
@@ -779,6 +774,17 @@ static coffee_status assemble_batch(int precision, const coffee_segment* segs, i
     int devid = 0;
     if (hipGetDevice(&devid) != hipSuccess) return COFFEE_E_HIP;
     const int esz = precision == COFFEE_FP64 ? 8 : 4;
+    const int ncu = num_cu(devid);
+    // Tasks no longer than a wave's share of the entries (FP32), a quarter of
+    // it (FP64: a task of the heaviest bin takes four times as long, and the
+    // batch ends with it), unless the segment sets them. Whole batch, packed, us,
+    // limit 64 / 128 / none: FP32 30,000 entries 52 / 63 / 63, 300,000 118 / 97 /
+    // 93, 1,000,000 308 / 227 / 209; FP64 85 / 134 / 211, 152 / 172 / 243, 429 /
+    // 338 / 359. Before (a workgroup on every CU and no limit): FP32 67, 97, 213,
+    // FP64 201, 278, 391, and 3,000 entries 57 -> 46 and 93 -> 76.
+    const int64_t share = nentries / ((int64_t)ncu * 4 * (precision == COFFEE_FP64 ? 4 : 1));
+    const int fit_cells = 64 * (int)std::min<int64_t>(16, std::max<int64_t>(1, share / 64));
+    int min_cells = 1024;
     int stage_elems = 8;  // staging area: 8 tensors of the largest bin that stages its stores
     for (int b = 0; b < nseg; ++b) {
         const coffee_segment& s = segs[b];
@@ -828,6 +834,8 @@ static coffee_status assemble_batch(int precision, const coffee_segment* segs, i
             int pt = 0;
             if (s.task_cells == 0) d.task_cells = tuned_packed(s.form, s.cell, s.degree, precision, &pt) ? pt : kPackedTaskCells;
         }
+        if (s.task_cells == 0) d.task_cells = std::min(d.task_cells, fit_cells);
+        min_cells = std::min(min_cells, d.task_cells);
         // the packed tiles stage 8 tensors when they fit 16 KiB (the
         // single-form engine's rule), the per-entry staged variant always
         const bool stages = packed ? 8 * d.nn * esz <= 16384 : d.variant == 0;
@@ -856,7 +864,6 @@ static coffee_status assemble_batch(int precision, const coffee_segment* segs, i
     a.boff = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(workspace) + kWsHeader + kWsArgs + kWsSlices);
     a.bcell = reinterpret_cast<int32_t*>(a.boff + nentries);
     hipStream_t s = (hipStream_t)hip_stream;
-    const int ncu = num_cu(devid);
     hipLaunchKernelGGL(dev::k_bin_count, dim3(a.nslices), dim3(256), 0, s, a);
     hipLaunchKernelGGL(dev::k_bin_scan, dim3(nseg), dim3(dev::kScanThreads), 0, s, a);
     hipLaunchKernelGGL(dev::k_bin_scatter, dim3(a.nslices), dim3(256), 0, s, a);
@@ -870,7 +877,8 @@ static coffee_status assemble_batch(int precision, const coffee_segment* segs, i
         return COFFEE_E_HIP;
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 256, lds) != hipSuccess || nb <= 0) nb = 1;
-    const int grid = ncu * nb * std::max(1, batch_grid_mult());
+    const int64_t tasks = nentries / min_cells + nseg;  // no more than this
+    const int grid = (int)std::min<int64_t>((int64_t)ncu * nb * std::max(1, batch_grid_mult()), (tasks + 3) / 4);
     if (precision == COFFEE_FP64)
         hipLaunchKernelGGL(dev::k_batch<dev::PREC_F64>, dim3(grid), dim3(256), lds, s,
                            (const dev::BatchArgs*)a.self, stage_elems);

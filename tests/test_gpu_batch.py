@@ -314,3 +314,22 @@ def test_batch_cell_major_field(cf, packed):
         b = cf.coffee_assemble_batch(cm, seg_of, cell_of, offs, mb.total_elems, precision="fp64")
     torch.cuda.synchronize()
     np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("entries", [14, 1400, 140_000, 560_000])
+def test_batch_task_size_by_entries(cf, precision, entries):
+    """Tasks sized by the number of entries (and the grid by the tasks): equal
+    to tasks of a given size bit for bit, both layouts."""
+    import torch
+    k = entries // 14
+    n_tri, n_tet = int((4 * k) ** 0.5) + 2, int(k ** (1 / 3)) + 2
+    mb = I.mixed_batch(n_tri=n_tri, n_tet=n_tet, tri_counts=(2 * k,) * 4, tet_counts=(2 * k,) * 3, seed=entries)
+    res = []
+    for task_cells in (0, 1024):
+        segs, (seg_of, cell_of, offs) = device_batch(cf, mb, 0, task_cells)
+        got = cf.coffee_assemble_batch(segs, seg_of, cell_of, offs, mb.total_elems, precision=precision)
+        gotp, poff = cf.coffee_assemble_batch_packed(segs, seg_of, cell_of, mb.total_elems, precision=precision)
+        res.append((got.cpu().numpy(), gotp.cpu().numpy(), poff.cpu().numpy()))
+    for a, b in zip(*res):
+        np.testing.assert_array_equal(a, b)
