@@ -560,6 +560,15 @@ __device__ __forceinline__ void prism_contract(const double* gt, const double* w
                     ah[c][t] = (__bf16)x;
                     al[c][t] = (__bf16)(x - (float)ah[c][t]);
                 }
+                if constexpr (T == 1) {
+                    // mass: two of the unused slots take the third part of the
+                    // coefficient, against the table's value, and the
+                    // coefficient, against the third part of that
+                    const float x = C::REM == 0 || i < C::NI ? (float)cf[0] : 0.0f;
+                    ah[c][1] = (__bf16)(x - (float)ah[c][0] - (float)al[c][0]);
+                    ah[c][2] = ah[c][0];
+                    al[c][2] = al[c][0];
+                }
             }
 #pragma unroll
             for (int t = 0; t < NT; ++t)
@@ -946,9 +955,11 @@ void prism_fac_pack(const std::vector<ld> (&R)[2], int prec, std::vector<char>& 
                     if (C::BF) {
                         // block s / 2 of four points, slot = type; hi, then lo
                         for (int k = 0; k < 8; ++k) {
-                            const float x = (float)val(k, 4 * (s / 2) + g, u);
-                            const uint16_t hi = bf16_bits_host(x);
-                            const uint16_t h = s % 2 == 0 ? hi : bf16_bits_host(x - bf16_float_host(hi));
+                            const float x = (float)val(T == 1 && k < 3 ? 0 : k, 4 * (s / 2) + g, u);
+                            const uint16_t hi = bf16_bits_host(x), lo = bf16_bits_host(x - bf16_float_host(hi));
+                            uint16_t h = s % 2 == 0 ? hi : lo;
+                            if (T == 1 && k == 2)  // mass: the third part
+                                h = s % 2 == 0 ? bf16_bits_host(x - bf16_float_host(hi) - bf16_float_host(lo)) : 0;
                             put(&h, 2);
                         }
                     } else {
