@@ -80,7 +80,9 @@ PEAK_TF = {"mfma_f64": 78.6, "mfma_f32": 157.3, "mfma_bf16x3": 2500.0 / 3.0, "va
 def svk_work(d: int, p: int, form: str, prec: str) -> dict:
     """Flops per cell (2 per multiply-add) that each SVK kernel executes, by
     the unit that executes them. Points: 1 at P1 (the integrand is constant),
-    the symmetric rule at P2 (6 triangle / 14 tetrahedron points)."""
+    the symmetric rule at P2 (6 triangle / 14 tetrahedron points). FP64 and
+    FP32 energy and residual take the displacement gradient at the nv nodes of
+    degree p - 1 once per cell and interpolate it at the points."""
     ns, D, nb = n_scalar(d, p), d, d * (d + 1) // 2
     nq = 1 if p == 1 else {2: 6, 3: 14}[d]
     U = 2 * D * D * ns                                   # reference displacement gradient
@@ -88,10 +90,18 @@ def svk_work(d: int, p: int, form: str, prec: str) -> dict:
     P = 2 * D ** 3                                       # P = F S
     if prec in ("fp64", "fp32"):
         unit = "valu_f64" if prec == "fp64" else "valu_f32"
+        nv = 1 if p == 1 else D + 1
+        nodes = U + nv * 2 * D ** 3                      # reference gradients at the nodes, times K
+        point = 2 * D * D * nv + pt - 2 * D ** 3         # interpolation, E, S, psi
         if form == "svk_energy":
-            return {unit: nq * (U + pt + P)}
+            return {"valu_f64": nodes, unit: nq * point} if unit != "valu_f64" else {unit: nodes + nq * point}
         if form == "svk_residual":
-            return {unit: nq * (U + pt + P + 2 * D ** 3 + 2 * D * D * ns)}
+            r = nq * (point + P + 2 * D * D * nv) + nodes
+            return {"valu_f64": nodes, unit: r} if unit != "valu_f64" else {unit: nodes + r}
+        if (D, p) == (3, 2):
+            # moments of the quadratic tangent: 2,300 FP64 vector operations
+            # per half block in both precisions, each a multiply-add's slot
+            return {"valu_f64": 2.0 * 2300 * 2 * nb}
         # Jacobian: F, S and S^ = K S K^T once per (cell, point); per block
         # k1, k2, F.F, H, the row products dphi^T H and the rank updates of the
         # block's n x n entries
@@ -116,16 +126,25 @@ def svk_work(d: int, p: int, form: str, prec: str) -> dict:
 
 def prism_work(w, prec: str) -> dict:
     """Prisms (non-affine): per point, J, det J, K = J^-1, K K^T and the
-    mass factor on the FP64 vector units (about 150 flops), then the
+    mass factor on the FP64 vector units (about 150 flops). Degree 1: the
     contraction over K = nq x (terms per point) for the n(n+1)/2 unique
-    entries on the matrix cores of the precision."""
+    entries on the matrix cores of the precision. Degrees 2 and 3, factored
+    over triangle and interval: per pair b <= b' of interval dofs the sum over
+    the interval points (vector FP64), then the contraction over (triangle
+    point, term type) for the triangle products (all of them for b < b', the
+    unique ones for b = b'); BF16X3 takes four products instead of three."""
     p, form = w.degree, w.form
-    ns = (p + 1) * (p + 2) // 2 * (p + 1)
+    nt, l = (p + 1) * (p + 2) // 2, p + 1
+    ns = nt * l
     m = (w.quad_degree + 2) // 2
     nq = m * m * m
-    jq = {"mass": 1, "helmholtz": 7, "diffusion": 6}[form]
     mm = {"fp64": "mfma_f64", "fp32": "mfma_f32", "bf16x3": "mfma_bf16x3"}[prec]
-    return {mm: 2.0 * nq * jq * ns * (ns + 1) / 2, "valu_f64": 150.0 * nq}
+    if p == 1:
+        jq = {"mass": 1, "helmholtz": 7, "diffusion": 6}[form]
+        return {mm: 2.0 * nq * jq * ns * (ns + 1) / 2, "valu_f64": 150.0 * nq}
+    off, t0, t1 = l * (l - 1) // 2, (1 if form == "mass" else 8), (1 if form == "mass" else 6)
+    f = 2.0 * m * m * (off * t0 * nt * nt + l * t1 * nt * (nt + 1) / 2)
+    return {mm: f * (4 / 3 if prec == "bf16x3" else 1), "valu_f64": 150.0 * nq + 2.0 * nq * (off * t0 + l * t1)}
 
 
 def work_model(w, prec: str) -> dict:
