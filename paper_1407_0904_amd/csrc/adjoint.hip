@@ -451,17 +451,22 @@ __global__ __launch_bounds__(256, (D == 3 && P == 2) ? 1 : 2) void k_adjoint_ela
                 A.det_f1[cell * NF + r] = sd * ad * lmb[r];
             }
         } else if (valid && !det) {
+            static_assert(NF == D + 1, "a coefficient dof per vertex");
+            unsigned long long kv[D + 1];
 #pragma unroll
-            for (int r = 0; r < NF; ++r) {
-                const double m = sd * ad * mub[r], q = sd * ad * lmb[r];
-                if (shared_keys) {
-                    // vertex r: coordinates and both coefficients in one slot
-                    const int h = combine_slot<TS>(ckx[wave], (unsigned long long)ix.v[r]);
-                    if (h >= 0) {
+            for (int r = 0; r <= D; ++r) kv[r] = (unsigned long long)ix.v[r];
+            if (shared_keys) {
+                // vertex r: coordinates and both coefficients in one slot
+                int h[D + 1];
+                combine_slots<TS>(ckx[wave], kv, h);
 #pragma unroll
-                        for (int i = 0; i < D; ++i) atomicAdd(&cvx[wave][h * D + i], vx[r][i]);
-                        atomicAdd(&cvf[wave][0][h], m);
-                        atomicAdd(&cvf[wave][1][h], q);
+                for (int r = 0; r <= D; ++r) {
+                    const double m = sd * ad * mub[r], q = sd * ad * lmb[r];
+                    if (h[r] >= 0) {
+#pragma unroll
+                        for (int i = 0; i < D; ++i) atomicAdd(&cvx[wave][h[r] * D + i], vx[r][i]);
+                        atomicAdd(&cvf[wave][0][h[r]], m);
+                        atomicAdd(&cvf[wave][1][h[r]], q);
                     } else {
 #pragma unroll
                         for (int i = 0; i < D; ++i)
@@ -469,14 +474,20 @@ __global__ __launch_bounds__(256, (D == 3 && P == 2) ? 1 : 2) void k_adjoint_ela
                         if (A.grad_f0) atomicAdd(A.grad_f0 + ix.v[r], m);
                         if (A.grad_f1) atomicAdd(A.grad_f1 + ix.v[r], q);
                     }
-                } else {
-                    if (A.grad_coords)
-                        combine_add<D, TS>(ckx[wave], cvx[wave], (unsigned long long)ix.v[r], vx[r], A.grad_coords);
-                    const int64_t i0 = A.L.f0.map ? (int64_t)ix.f0[r] : cell * NF + r;
-                    const int64_t i1 = A.L.f1.map ? (int64_t)ix.f1[r] : cell * NF + r;
-                    if (A.grad_f0) combine_add<1, TS>(ckf[wave][0], cvf[wave][0], (unsigned long long)i0, &m, A.grad_f0);
-                    if (A.grad_f1) combine_add<1, TS>(ckf[wave][1], cvf[wave][1], (unsigned long long)i1, &q, A.grad_f1);
                 }
+            } else {
+                unsigned long long k0[NF], k1[NF];
+                double m[NF][1], q[NF][1];
+#pragma unroll
+                for (int r = 0; r < NF; ++r) {
+                    k0[r] = (unsigned long long)(A.L.f0.map ? (int64_t)ix.f0[r] : cell * NF + r);
+                    k1[r] = (unsigned long long)(A.L.f1.map ? (int64_t)ix.f1[r] : cell * NF + r);
+                    m[r][0] = sd * ad * mub[r];
+                    q[r][0] = sd * ad * lmb[r];
+                }
+                if (A.grad_coords) combine_add<D, TS>(ckx[wave], cvx[wave], kv, vx, A.grad_coords);
+                if (A.grad_f0) combine_add<1, TS>(ckf[wave][0], cvf[wave][0], k0, m, A.grad_f0);
+                if (A.grad_f1) combine_add<1, TS>(ckf[wave][1], cvf[wave][1], k1, q, A.grad_f1);
             }
         }
         if (!det) {

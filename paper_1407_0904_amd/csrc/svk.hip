@@ -208,19 +208,21 @@ __device__ inline void svk_scatter_cell(const SvkArgs& A, bool det, int64_t cell
         return;
     }
     if (A.grad_coords) {
+        unsigned long long key[D + 1];
 #pragma unroll
-        for (int v = 0; v <= D; ++v)
-            combine_add<D, TS>(ckeys, cvals, (unsigned long long)vid[v], vx[v], A.grad_coords);
+        for (int v = 0; v <= D; ++v) key[v] = (unsigned long long)vid[v];
+        combine_add<D, TS>(ckeys, cvals, key, vx, A.grad_coords);
     }
     if constexpr (U) {
+        unsigned long long key[NS];
+        double v[NS][D];
 #pragma unroll
         for (int r = 0; r < NS; ++r) {
-            const unsigned long long key = A.u.map ? (unsigned long long)uid[r] : (unsigned long long)(cell * NS + r);
-            double v[D];
+            key[r] = A.u.map ? (unsigned long long)uid[r] : (unsigned long long)(cell * NS + r);
 #pragma unroll
-            for (int c = 0; c < D; ++c) v[c] = f * (double)g[c * NS + r];
-            combine_add<D, TU>(ukeys, uvals, key, v, A.grad_u);
+            for (int c = 0; c < D; ++c) v[r][c] = f * (double)g[c * NS + r];
         }
+        combine_add<D, TU>(ukeys, uvals, key, v, A.grad_u);
     }
 }
 
