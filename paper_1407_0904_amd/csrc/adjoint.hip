@@ -273,8 +273,13 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
 // (reference gradient) K, the derivative in J is (S I - T) K^T,
 //     T = |det J| sum_k (Hlam_k^T Wu_k + Hu_k^T Wlam_k).
 // What is left is the read of lam and u, 480 bytes per cell: component by
-// component through LDS (coalesced 8-byte reads, the next component in flight
-// while the current one is used), into rows of odd length per cell.
+// component through LDS (coalesced 8-byte reads) into rows of odd length per
+// cell; and the scatter-adds. Of the 37,000 cycles a wave took for 64 P2
+// tetrahedra the arithmetic was 3,000, the loads 10,000 to 14,000 (behind the
+// previous cells' atomics), the combining 9,000, its flush 9,000. A persistent
+// grid (one workgroup per CU and residency) now has all loads of the next
+// cells in flight over the combining, complete before the flush issues its
+// atomics: 170 -> 128 us (eight workgroups per CU 153); P2 triangles 49 -> 34.
 
 // The H of P2 tetrahedra (144 registers) and what is formed from them need one
 // wave per SIMD: at two, 255 registers spilled (352 us against 190).
@@ -293,25 +298,35 @@ __global__ __launch_bounds__(256, (D == 3 && P == 2) ? 1 : 2) void k_adjoint_ela
     const bool det = A.det_x != nullptr;  // same in every lane, as the next
     const bool shared_keys = A.L.f0.map == A.L.c2v && A.L.f1.map == A.L.c2v;  // the fields' dofs are the vertices
     // wave-uniform loop: every lane takes part in the staging, clear and flush
-    for (int64_t base = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) - lane; base < A.L.ncells;
-         base += (int64_t)gridDim.x * blockDim.x) {
-        const bool valid = base + lane < A.L.ncells;
-        const int last = A.L.ncells - base < 64 ? (int)(A.L.ncells - base) - 1 : 63;
-        const int64_t cell = base + (lane < last ? lane : last);
-        const double* src[2] = {A.lam + base * N, A.u + base * N};
-        double pre[NS];  // component c of the wave's cells: flat entry 64 i + lane
-        auto fetch = [&](const double* x, int c) {
+    int64_t base = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) - lane;
+    if (base >= A.L.ncells) return;  // wave-uniform; no workgroup barrier follows
+    CellIdx<F_ELAST, D, FD> ix, nx;  // of this unit and the next
+    CellRaw<F_ELAST, D, FD> raw;
+    double pre[2][D][NS];  // component c of lam, u of the wave's cells: flat entry 64 i + lane
+    auto cell_at = [&](int64_t b) { return b + lane < A.L.ncells ? b + lane : A.L.ncells - 1; };
+    // all of them are in flight at once; `more` false (no next unit): those of
+    // one cell, so that the registers have one definition and little is read
+    auto fetch = [&](int64_t b, bool more) {
+        load_idx<F_ELAST, D, FD>(A.L, cell_at(b), nx);
+        const int last = !more ? 0 : (A.L.ncells - b < 64 ? (int)(A.L.ncells - b) - 1 : 63);
+        int ln = lane;  // opaque: the offsets are formed here, not kept across the loop
+        asm volatile("" : "+v"(ln));
 #pragma unroll
-            for (int i = 0; i < NS; ++i) {
-                const int t = 64 * i + lane, e = t / NS, a = t - e * NS;
-                pre[i] = gload(x + (e < last ? e : last) * N + c * NS + a);
-            }
-        };
-        CellIdx<F_ELAST, D, FD> ix;
-        CellRaw<F_ELAST, D, FD> raw;
-        load_idx<F_ELAST, D, FD>(A.L, cell, ix);
-        fetch(src[0], 0);
-        load_raw<F_ELAST, D, FD>(A.L, cell, ix, raw);
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int c = 0; c < D; ++c)
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    const int t = 64 * i + ln, e = t / NS, a = t - e * NS;
+                    pre[f][c][i] = gload((f == 0 ? A.lam : A.u) + b * N + (e < last ? e : last) * N + c * NS + a);
+                }
+    };
+    fetch(base, true);
+    load_raw<F_ELAST, D, FD>(A.L, cell_at(base), nx, raw);
+    for (; base < A.L.ncells; base += (int64_t)gridDim.x * blockDim.x) {
+        const bool valid = base + lane < A.L.ncells;
+        const int64_t cell = cell_at(base), next = base + (int64_t)gridDim.x * blockDim.x;
+        ix = nx;
         CellData<F_ELAST, D, FD, double> cd;
         cell_from_raw<F_ELAST, D, FD>(raw, cd);
         const auto& K = cd.g.K;
@@ -325,10 +340,8 @@ __global__ __launch_bounds__(256, (D == 3 && P == 2) ? 1 : 2) void k_adjoint_ela
 #pragma unroll
                 for (int i = 0; i < NS; ++i) {
                     const int t = 64 * i + lane, e = t / NS;
-                    stage[e * ROW + t - e * NS] = pre[i];
+                    stage[e * ROW + t - e * NS] = pre[f][c][i];
                 }
-                if (c + 1 < D) fetch(src[f], c + 1);
-                else if (f == 0) fetch(src[1], 0);
                 wave_sync();
                 double v[NS], g[NV][D];
 #pragma unroll
@@ -440,6 +453,11 @@ __global__ __launch_bounds__(256, (D == 3 && P == 2) ? 1 : 2) void k_adjoint_ela
             }
             vx[0][i] = sd * x0;
         }
+        // the next unit's loads, complete before this one's atomics are issued
+        // (one in-order counter: a load behind them would wait for them)
+        const int64_t ahead = next < A.L.ncells ? next : base;
+        fetch(ahead, next < A.L.ncells);
+        __builtin_amdgcn_sched_barrier(0);
         if (valid && det) {
 #pragma unroll
             for (int v = 0; v <= D; ++v)
@@ -490,6 +508,13 @@ __global__ __launch_bounds__(256, (D == 3 && P == 2) ? 1 : 2) void k_adjoint_ela
                 if (A.grad_f1) combine_add<1, TS>(ckf[wave][1], cvf[wave][1], k1, q, A.grad_f1);
             }
         }
+        load_raw<F_ELAST, D, FD>(A.L, cell_at(ahead), nx, raw);
+#pragma unroll
+        for (int v = 0; v <= D; ++v)
+#pragma unroll
+            for (int i = 0; i < D; ++i) asm volatile("" ::"v"(raw.x[v][i]));
+#pragma unroll
+        for (int r = 0; r < NF; ++r) asm volatile("" ::"v"(raw.f0[r]), "v"(raw.f1[r]));
         if (!det) {
             wave_sync();
             const unsigned long long* k0 = shared_keys ? ckx[wave] : ckf[wave][0];
@@ -504,7 +529,7 @@ __global__ __launch_bounds__(256, (D == 3 && P == 2) ? 1 : 2) void k_adjoint_ela
 
 }  // namespace dev
 
-typedef hipError_t (*AdjLaunch)(const dev::AdjArgs&, hipStream_t, int grid);
+typedef hipError_t (*AdjLaunch)(const dev::AdjArgs&, hipStream_t, int64_t blocks, int ncu);
 struct AdjEntry {
     int form, dim, p, fd;
     AdjLaunch launch;
@@ -513,11 +538,14 @@ struct AdjEntry {
 // Elasticity at the registered degrees (1 and 2, P1 coefficients) uses the
 // node kernel, whose table AdjArgs::R is c_rkl (node_weights).
 template <int FORM, int D, int P, int FD>
-hipError_t launch_adjoint(const dev::AdjArgs& a, hipStream_t s, int grid) {
-    if constexpr (FORM == dev::F_ELAST)
+hipError_t launch_adjoint(const dev::AdjArgs& a, hipStream_t s, int64_t blocks, int ncu) {
+    if constexpr (FORM == dev::F_ELAST) {
+        const int grid = (int)std::min<int64_t>(blocks, (int64_t)ncu * (D == 3 && P == 2 ? 1 : 2));
         hipLaunchKernelGGL((dev::k_adjoint_elast<D, P, FD>), dim3(grid), dim3(256), 0, s, a);
-    else
+    } else {
+        const int grid = (int)std::min<int64_t>(blocks, (int64_t)ncu * 8);
         hipLaunchKernelGGL((dev::k_adjoint_linear<FORM, D, P, FD>), dim3(grid), dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 
@@ -666,8 +694,7 @@ coffee_status adjoint_linear(int form, int cell, int degree, int q, int fd, cons
         a.det_f1 = ncoeff >= 2 ? det[2].local : nullptr;
     }
     const int64_t blocks = (ncells + 255) / 256;
-    const int grid = (int)std::min<int64_t>(blocks, (int64_t)num_cu(dev) * 8);
-    if (e->launch(a, (hipStream_t)hip_stream, grid) != hipSuccess) return COFFEE_E_HIP;
+    if (e->launch(a, (hipStream_t)hip_stream, blocks, num_cu(dev)) != hipSuccess) return COFFEE_E_HIP;
     return COFFEE_OK;
 }
 

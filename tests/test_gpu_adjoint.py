@@ -299,3 +299,36 @@ def test_elasticity_adjoint_ragged_counts_and_maps(cf, oracle, d, p, q):
             for a, b in zip(hf, gf):
                 assert rel(a.reshape(b.shape), b) < 1e-11, (count, kind)
             assert abs(float(cv.sum()) - float(np.sum(S))) <= 1e-11 * float(cv.abs().sum())
+
+
+@pytest.mark.parametrize("d,p,n,extra", [(3, 2, 23, 65), (3, 1, 28, 1), (2, 2, 260, 127)])
+def test_elasticity_adjoint_several_units_per_wave(cf, d, p, n, extra):
+    """More cells than one pass of the grid takes, with a ragged end: the per-cell values equal those of calls on
+    parts that one pass takes bit for bit, the gradients their sum (atomic order: 1e-12 of the largest)."""
+    import torch
+    from gpu_util import to_dev
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    part = 256 * cu * (1 if (d, p) == (3, 2) else 2)
+    rng = np.random.default_rng(5 + d + p)
+    mesh = I.make_mesh(d, n, 0.1, rng)
+    count = min(part + extra, mesh.ncells)
+    sub = I.Mesh(d, mesh.n, mesh.coords, np.ascontiguousarray(mesh.cells[:count]))
+    coords, c2v, _ = to_dev(sub, [])
+    dev = c2v.device
+    vals = [torch.as_tensor(rng.uniform(1, 10, (mesh.nvert, 1)), device=dev) for _ in range(2)]
+    N = d * I.n_scalar_dofs(d, p)
+    lam, u = (torch.as_tensor(rng.standard_normal((count, N)), device=dev) for _ in range(2))
+
+    def call(a, b):
+        cells = c2v[a:b].contiguous()
+        fs = [cf.DeviceField(v, cells, 1, 1) for v in vals]
+        cv = torch.empty(b - a, dtype=torch.float64, device=dev)
+        g, h = cf.coffee_assemble_adjoint("elasticity", d, p, coords, cells, coeffs=fs, lam=lam[a:b].contiguous(),
+                                          u=u[a:b].contiguous(), cell_value=cv)
+        return cv, g, *h
+
+    whole, half = call(0, count), count // 2
+    lo, hi = call(0, half), call(half, count)
+    assert torch.equal(whole[0], torch.cat((lo[0], hi[0])))
+    for w, x, y in zip(whole[1:], lo[1:], hi[1:]):
+        assert float((w - x - y).abs().max()) <= 1e-12 * float(w.abs().max())
