@@ -157,26 +157,48 @@ __device__ inline void svk_point(const T (&H)[D][D], T mu, T lm, T* psi, T (&Pou
 }
 
 template <int D, int NS>
-__device__ inline void svk_load(const SvkArgs& A, int64_t cell, Geom<D>& g, double (&uv)[NS * D],
-                                int (&vid)[D + 1], int (&uid)[NS]) {
-    double x[D + 1][D];
+struct SvkCell {
+    int vid[D + 1], uid[NS];
+    double x[D + 1][D], u[NS * D];
+};
+
+template <int D, int NS>
+__device__ inline void svk_load_ids(const SvkArgs& A, int64_t cell, SvkCell<D, NS>& c) {
 #pragma unroll
-    for (int v = 0; v <= D; ++v) vid[v] = A.c2v[cell * (D + 1) + v];
+    for (int v = 0; v <= D; ++v) c.vid[v] = A.c2v[cell * (D + 1) + v];
+    if (A.u.map) {
+#pragma unroll
+        for (int r = 0; r < NS; ++r) c.uid[r] = A.u.map[cell * NS + r];
+    }
+}
+
+template <int D, int NS>
+__device__ inline void svk_load_values(const SvkArgs& A, int64_t cell, SvkCell<D, NS>& c) {
 #pragma unroll
     for (int v = 0; v <= D; ++v)
 #pragma unroll
-        for (int i = 0; i < D; ++i) x[v][i] = A.coords[(int64_t)vid[v] * D + i];
-    geometry_from_coords<D>(x, g);
-    if (A.u.map) {
-#pragma unroll
-        for (int r = 0; r < NS; ++r) uid[r] = A.u.map[cell * NS + r];
-    }
+        for (int i = 0; i < D; ++i) c.x[v][i] = A.coords[(int64_t)c.vid[v] * D + i];
 #pragma unroll
     for (int r = 0; r < NS; ++r) {
-        const int64_t base = A.u.map ? (int64_t)uid[r] * D : (cell * NS + r) * D;
+        const int64_t base = A.u.map ? (int64_t)c.uid[r] * D : (cell * NS + r) * D;
 #pragma unroll
-        for (int i = 0; i < D; ++i) uv[r * D + i] = A.u.values[base + i];
+        for (int i = 0; i < D; ++i) c.u[r * D + i] = A.u.values[base + i];
     }
+}
+
+template <int D, int NS>
+__device__ inline void svk_load(const SvkArgs& A, int64_t cell, Geom<D>& g, double (&uv)[NS * D],
+                                int (&vid)[D + 1], int (&uid)[NS]) {
+    SvkCell<D, NS> c;
+    svk_load_ids<D, NS>(A, cell, c);
+    svk_load_values<D, NS>(A, cell, c);
+    geometry_from_coords<D>(c.x, g);
+#pragma unroll
+    for (int v = 0; v <= D; ++v) vid[v] = c.vid[v];
+#pragma unroll
+    for (int r = 0; r < NS; ++r) uid[r] = c.uid[r];
+#pragma unroll
+    for (int r = 0; r < NS * D; ++r) uv[r] = c.u[r];
 }
 
 typedef unsigned int svk_u32x4 __attribute__((ext_vector_type(4)));
@@ -287,6 +309,16 @@ __global__ __launch_bounds__(256) void k_svk_vec(SvkArgs A) {
     __shared__ unsigned long long ckeys[4][TS], ukeys[4][TU];
     __shared__ double cvals[4][TS * D], uvals[4][TU * D];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // reverse pass: the next cell's dofs and values, loaded during the current
+    // one's combining and complete before its flush
+    SvkCell<D, NS> nx;
+    auto cell_at = [&](int64_t b) { return b + lane < A.ncells ? b + lane : A.ncells - 1; };
+    if constexpr (REV) {
+        const int64_t b = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) - lane;
+        if (b >= A.ncells) return;  // wave-uniform; no workgroup barrier follows
+        svk_load_ids<D, NS>(A, cell_at(b), nx);
+        svk_load_values<D, NS>(A, cell_at(b), nx);
+    }
     // wave-uniform loop (every lane takes part in the table's clear and flush)
     for (int64_t base = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) - lane; base < A.ncells;
          base += (int64_t)gridDim.x * blockDim.x) {
@@ -302,8 +334,16 @@ __global__ __launch_bounds__(256) void k_svk_vec(SvkArgs A) {
         T H[NV][D][D];  // displacement gradient at the nodes
         int vid[D + 1], uid[NS];
         {
-            double uvd[NS * D];
-            svk_load<D, NS>(A, cell, g, uvd, vid, uid);
+            if constexpr (!REV) {
+                svk_load_ids<D, NS>(A, cell, nx);
+                svk_load_values<D, NS>(A, cell, nx);
+            }
+            geometry_from_coords<D>(nx.x, g);
+            const double(&uvd)[NS * D] = nx.u;
+#pragma unroll
+            for (int v = 0; v <= D; ++v) vid[v] = nx.vid[v];
+#pragma unroll
+            for (int r = 0; r < NS; ++r) uid[r] = nx.uid[r];
 #pragma unroll
             for (int c = 0; c < D; ++c) {
                 double v[NS], gr[NV][D];
@@ -415,9 +455,26 @@ __global__ __launch_bounds__(256) void k_svk_vec(SvkArgs A) {
                 }
                 vx[0][i] = sd * x0;
             }
+            const int64_t next = base + (int64_t)gridDim.x * blockDim.x;
+            const bool more = next < A.ncells;  // wave-uniform
+            // (no next cell: zeros, so that the registers hold no old values)
+            if (more) svk_load_ids<D, NS>(A, cell_at(next), nx);
+            else nx = SvkCell<D, NS>{};
             if (valid) {
                 svk_scatter_cell<D, NS, TS, TU, MODE == 3>(A, det, cell, vid, uid, vx, res, sd * ad, ckeys[wave],
                                                            cvals[wave], ukeys[wave], uvals[wave]);
+            }
+            // (one in-order counter: a load behind the atomics would wait for them)
+            if (more) {
+                svk_load_values<D, NS>(A, cell_at(next), nx);
+#pragma unroll
+                for (int v = 0; v <= D; ++v)
+#pragma unroll
+                    for (int i = 0; i < D; ++i) asm volatile("" ::"v"(nx.x[v][i]));
+#pragma unroll
+                for (int r = 0; r < NS * D; ++r) asm volatile("" ::"v"(nx.u[r]));
+            } else {
+                nx = SvkCell<D, NS>{};
             }
             if (!det) {
                 wave_sync();
@@ -1386,13 +1443,25 @@ template <int D, int P, int NQ>
 hipError_t launch_svk(int form, int precision, const dev::SvkArgs& a, hipStream_t s, int ncu, bool reverse) {
     const int64_t blocks = (a.ncells + 255) / 256;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(blocks, (int64_t)ncu * 8));
+    // reverse pass: the workgroups that fit, by registers and LDS (both
+    // gradients, us: P2 tetrahedra, 196,608 / 2,058,000 cells: one per CU 54 and
+    // 495, two 58 and 494, eight 63 and 519; P1 tetrahedra, 196,608 /
+    // 1,296,000: two 18 and 93, three 19 and 108, eight 20 and 96; P1
+    // triangles, 720,000: one 37, two 29, three 25, eight 27). Loading each
+    // cell's values behind the previous one's atomics, eight per CU: P2
+    // tetrahedra 59 and 557, P1 22 and 95, P1 triangles 29, P2 triangles,
+    // 180,000, 21 -> 18.
+    auto rgrid = [&](int mode) {
+        const int fit = D == 2 ? 3 : (P == 2 && mode == 3 ? 1 : 2);
+        return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, (int64_t)ncu * fit));
+    };
     if (reverse) {
         if (form == COFFEE_SVK_RESIDUAL)
             hipLaunchKernelGGL((dev::k_svk_res_adj<D, P, NQ>), dim3(grid), dim3(256), 0, s, a);
         else if (a.grad_u || a.det_u)
-            hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 3, double>), dim3(grid), dim3(256), 0, s, a);
+            hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 3, double>), dim3(rgrid(3)), dim3(256), 0, s, a);
         else
-            hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 2, double>), dim3(grid), dim3(256), 0, s, a);
+            hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 2, double>), dim3(rgrid(2)), dim3(256), 0, s, a);
         return hipGetLastError();
     }
     const bool f64 = precision == COFFEE_FP64;

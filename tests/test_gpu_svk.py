@@ -334,3 +334,34 @@ def test_svk_jacobian_ragged_counts(cf, oracle, d, p, prec):
         for f in (mapped, cellmajor):
             got = assemble_gpu("svk_jacobian", sub, p, [f], constants=cst, precision=prec).cpu().numpy()
             assert cell_rel_err(got, ref) < TOL[prec], (count, f.cell_to_dof is None)
+
+
+@pytest.mark.parametrize("d,p,n,fit,extra", [(3, 2, 23, 1, 65), (3, 1, 28, 2, 1), (2, 2, 320, 3, 127)])
+def test_svk_energy_gradients_several_units_per_wave(cf, d, p, n, fit, extra):
+    """More cells than one pass of the grid takes, with a ragged end: the per-cell energies equal those of calls on
+    parts that one pass takes bit for bit, the gradients their sum (atomic order: 1e-12 of the largest)."""
+    import torch
+    from gpu_util import to_dev
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(11 + d + p)
+    mesh = I.make_mesh(d, n, 0.1, rng)
+    count = min(256 * cu * fit + extra, mesh.ncells)
+    sub = I.Mesh(d, mesh.n, mesh.coords, np.ascontiguousarray(mesh.cells[:count]))
+    coords, c2v, _ = to_dev(sub, [])
+    dev, ns = c2v.device, I.n_scalar_dofs(d, p)
+    ndofs = count * ns // 5 + ns
+    dofs = (torch.arange(count * ns, device=dev) % ndofs).to(torch.int32).reshape(count, ns)
+    vals = torch.as_tensor(0.05 * rng.standard_normal((ndofs, d)), device=dev)
+
+    def call(a, b):
+        u = cf.DeviceField(vals, dofs[a:b].contiguous(), p, d)
+        e = torch.empty(b - a, dtype=torch.float64, device=dev)
+        g, h = cf.coffee_assemble_adjoint("svk_energy", d, p, coords, c2v[a:b].contiguous(), coeffs=[u],
+                                          constants=(1.0, 2.0), cell_value=e)
+        return e, g, h[0]
+
+    whole, half = call(0, count), count // 2
+    lo, hi = call(0, half), call(half, count)
+    assert torch.equal(whole[0], torch.cat((lo[0], hi[0])))
+    for w, x, y in zip(whole[1:], lo[1:], hi[1:]):
+        assert float((w - x - y).abs().max()) <= 1e-12 * float(w.abs().max())
