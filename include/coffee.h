@@ -212,7 +212,8 @@ int64_t coffee_adjoint_workspace_size(int form, int cell, int degree, int64_t nv
  * multiple of 64, at most 1024) is how many of the bin's cells one wave takes
  * from the queue at a time. task_cells = 0 selects the autotuned pair for
  * this (form, shape, degree, precision) from the loaded tuning cache, else
- * (variant, 256). The bin's mesh must have at most 2^31 - 1 cells. */
+ * (variant, 256), with fewer cells where the batch would leave waves without
+ * a task. The bin's mesh must have at most 2^31 - 1 cells. */
 typedef struct {
     int32_t form, cell, degree, quad_degree;
     const double* coords;
