@@ -236,6 +236,8 @@ __device__ inline void svk_scatter_cell(const SvkArgs& A, bool det, int64_t cell
         combine_add<D, TS>(ckeys, cvals, key, vx, A.grad_coords);
     }
     if constexpr (U) {
+        // NULL: the caller skips this gradient (a full table adds to it directly)
+        if (!A.grad_u) return;
         unsigned long long key[NS];
         double v[NS][D];
 #pragma unroll

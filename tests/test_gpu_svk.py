@@ -365,3 +365,30 @@ def test_svk_energy_gradients_several_units_per_wave(cf, d, p, n, fit, extra):
     assert torch.equal(whole[0], torch.cat((lo[0], hi[0])))
     for w, x, y in zip(whole[1:], lo[1:], hi[1:]):
         assert float((w - x - y).abs().max()) <= 1e-12 * float(w.abs().max())
+
+
+@pytest.mark.parametrize("cellmajor", [True, False])
+@pytest.mark.parametrize("d,p", [(3, 1), (3, 2), (2, 1), (2, 2)])
+def test_svk_residual_adjoint_without_displacement_gradient(cf, d, p, cellmajor):
+    """The residual's reverse pass with the displacement gradient skipped (values alone; coordinates alone), with more
+    distinct dofs per wave than a combining table holds: what is left equals the full pass."""
+    import torch
+    from gpu_util import to_dev
+    rng = np.random.default_rng(490 + 10 * d + p)
+    mesh = I.make_mesh(d, 17 if d == 2 else 5, 0.1, rng)
+    count, ns = 257, I.n_scalar_dofs(d, p)
+    sub = I.Mesh(d, mesh.n, mesh.coords, np.ascontiguousarray(mesh.cells[rng.permutation(mesh.ncells)[:count]]))
+    coords, c2v, _ = to_dev(sub, [])
+    dev = coords.device
+    vals = torch.as_tensor(rng.normal(0, 0.05, (count * ns, d)), device=dev)
+    dofs = torch.as_tensor(rng.permutation(count * ns).astype(np.int32).reshape(count, ns), device=dev)
+    u = cf.DeviceField(vals[dofs.long()].contiguous() if cellmajor else vals, None if cellmajor else dofs, p, d)
+    lam = torch.as_tensor(rng.standard_normal((count, d * ns)), device=dev)
+    cv = [torch.empty(count, dtype=torch.float64, device=dev) for _ in range(3)]
+    full, _ = cf.coffee_assemble_adjoint("svk_residual", d, p, coords, c2v, coeffs=[u], lam=lam, cell_value=cv[0])
+    cf.coffee_assemble_adjoint("svk_residual", d, p, coords, c2v, coeffs=[u], lam=lam, cell_value=cv[1], grads=False)
+    only, _ = cf.coffee_assemble_adjoint("svk_residual", d, p, coords, c2v, coeffs=[u], lam=lam, cell_value=cv[2],
+                                         grad_coeffs=[None])
+    torch.cuda.synchronize()
+    assert torch.equal(cv[0], cv[1]) and torch.equal(cv[0], cv[2])
+    assert float((full - only).abs().max()) <= 1e-12 * float(full.abs().max())
