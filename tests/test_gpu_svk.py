@@ -318,7 +318,7 @@ def test_svk_energy_gradients_scattered_cells(cf, oracle, d, p):
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 @pytest.mark.parametrize("d,p", [(3, 1), (3, 2), (2, 2)])
-def test_svk_jacobian_ragged_counts(cf, oracle, d, p, prec):
+def test_svk_jacobian_counts_around_groups(cf, oracle, d, p, prec):
     """Jacobian at counts around the five-cell group and the twenty cells of a workgroup, through a dof map and
     cell-major, with large displacements (every term of the tangent matters)."""
     from gpu_util import TOL, assemble_gpu, cell_rel_err
