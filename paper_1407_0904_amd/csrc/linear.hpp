@@ -21,6 +21,8 @@
 
 #include <cstdint>
 
+#include "combine.hpp"
+
 namespace coffee {
 namespace dev {
 
@@ -619,37 +621,30 @@ __device__ inline void combine_clear(unsigned long long* keys, double* vals, int
     for (int i = 0; i < TS * NV; i += 64) vals[i + lane] = 0.0;
 }
 
-// First slot of a key: keys are hashed in groups of eight consecutive ones,
-// which keep their order inside the group, so that the flush finds
-// neighbouring dofs in neighbouring slots (both gradients of 2,058,000 P2
-// tetrahedra: 809 us with single keys hashed, 665 so).
-template <int TS>
-__device__ inline unsigned combine_hash(unsigned long long key) {
-    return ((unsigned)(((key >> 3) * 0x9E3779B97F4A7C15ull) >> 40) * 8u + (unsigned)(key & 7u)) & (TS - 1);
-}
-
 // The slots of M keys, inserted if they are new; -1 where the probe limit is
 // reached. The first probes of all keys are in flight together (with that and
 // the flush's joint reads, both gradients of 2,058,000 P2 tetrahedra 617 ->
 // 551 us, elasticity's of 663,552 181 -> 171, Helmholtz's of 384,000 156 ->
-// 147). What is left are the LDS adds themselves, five or so of a wave's lanes
-// on one address, and the atomics of the flush.
+// 147); the later ones, which few keys need, are not (all in flight: 196,608
+// P2 tetrahedra 49 -> 55 us). What is left are the LDS adds themselves, five
+// or so of a wave's lanes on one address, and the atomics of the flush.
 template <int TS, int M>
 __device__ inline void combine_slots(unsigned long long* keys, const unsigned long long (&key)[M], int (&slot)[M]) {
+    static_assert(TS >= 8 * kCombineProbes, "probes reach different slots");
     unsigned long long old[M];
 #pragma unroll
     for (int r = 0; r < M; ++r) {
-        slot[r] = (int)combine_hash<TS>(key[r]);
+        slot[r] = (int)combine_first(key[r], TS);
         old[r] = atomicCAS(&keys[slot[r]], kEmptyKey, key[r]);
     }
 #pragma unroll
     for (int r = 0; r < M; ++r)
         for (int t = 1; old[r] != kEmptyKey && old[r] != key[r]; ++t) {
-            if (t == 32) {
+            if (t == kCombineProbes) {
                 slot[r] = -1;
                 break;
             }
-            slot[r] = (slot[r] + 8) & (TS - 1);
+            slot[r] = (int)combine_next((unsigned)slot[r], TS);
             old[r] = atomicCAS(&keys[slot[r]], kEmptyKey, key[r]);
         }
 }
@@ -690,6 +685,9 @@ __device__ inline void combine_flush(const unsigned long long* keys, const doubl
                                      int lane) {
     constexpr int IT = TS * NV / 64, CH = IT % 6 == 0 ? 6 : (IT % 4 == 0 ? 4 : 1);
     static_assert(TS % 64 == 0, "whole passes");
+    // opaque: the slots of the passes are formed here, not kept in registers
+    // across the caller's loop (32 of them in the Burgers adjoint)
+    asm volatile("" : "+v"(lane));
 #pragma unroll
     for (int i0 = 0; i0 < IT; i0 += CH) {
         unsigned long long key[CH];
