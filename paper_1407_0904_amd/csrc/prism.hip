@@ -25,7 +25,7 @@
 // matrices leave through LDS as contiguous 16-byte stores (the staging area
 // reuses the G rows). Degrees 2 and 3 (k_prism_fac): the contraction is
 // factored over the triangle and the interval, the waves of a workgroup share
-// 32 cells, each taking pairs of interval dofs.
+// 16 cells (degree 2) or 32 (degree 3), each taking pairs of interval dofs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -422,11 +422,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // lines that the L2 evicts).
 //
 // Degree 2 is bound by its instructions and the phases of a workgroup, so the
-// small tile (21 KB of LDS, many workgroups per CU) matters: two tiles per
-// workgroup ran 613 us in FP64 with three waves, 640 to 780 with six.
-// Diffusion, against the contraction over (point, term): 524,288 P2 prisms
-// FP64 656 -> 494 us, FP32 372 -> 302, BF16X3 262 -> 269; 65,536 P3 prisms
-// FP64 765 -> 367, FP32 415 -> 217, BF16X3 215 -> 176.
+// small tile (25 KB of LDS, many workgroups per CU) matters: two tiles per
+// workgroup ran 613 us in FP64 with three waves, 640 to 780 with six. Its
+// gathers go through LDS, each value read by one thread: read by all threads
+// of a cell they took 25 to 60 us of the mass form's time (below, "all
+// gather"). 524,288 P2 prisms, us:
+//                          points and terms   all gather   as it is
+//   mass            FP64         290              313          262
+//   mass, field     FP64         315              346          289
+//   mass            BF16X3       189              250          189
+//   mass, field     BF16X3       194              261          195
+//   diffusion       FP64         667              497          490
+//   diffusion       FP32         376              301          299
+//   diffusion       BF16X3       267              278          269
+// (the BF16X3 mass form also packs its products: kMassParts). 65,536 P3
+// prisms: diffusion FP64 765 -> 367, FP32 415 -> 217, BF16X3 215 -> 175; mass
+// BF16X3 108 -> 129 with one product per slot, 101 packed.
+
 // Workgroup barrier that orders LDS accesses only. Nothing passes between the
 // threads through global memory, and __syncthreads would also wait until
 // every outstanding store has reached memory and every prefetch has arrived
@@ -436,6 +448,14 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
+
+// Mass form in BF16X3: coefficient and table value are split in three bf16
+// parts (0 hi, 1 lo, 2 third), and the six products that matter fill six of
+// the 8 KS slots of a lane for each of its points: {part of the coefficient,
+// part of the table}. The leftover point's are spread over three lane groups,
+// two slots each: kMassRest[lane group][slot].
+constexpr int kMassParts[6][2] = {{0, 0}, {1, 0}, {0, 1}, {2, 0}, {0, 2}, {1, 1}};
+constexpr int kMassRest[3][2] = {{0, 1}, {2, 3}, {4, 5}};  // indices into kMassParts
 
 template <int FORM, int P, int FD, int PREC>
 struct PrismFacCfg {
@@ -459,8 +479,10 @@ struct PrismFacCfg {
     static constexpr int FULLB = NI / 4, REM = NI % 4;
     static_assert(REM <= 1, "one leftover point");
     // k-steps (BF16X3: blocks of four points, eight type slots each, with a hi
-    // and a lo fragment)
+    // and a lo fragment; the mass form, with one type, packs the products of
+    // its splits over the slots instead: kMassParts)
     static constexpr int steps(int kind) {
+        if (BF && types(kind) == 1) return (6 * FULLB + 2 * REM + 7) / 8;
         return BF ? 2 * ((NI + 3) / 4) : FULLB * types(kind) + (REM ? (types(kind) + 3) / 4 : 0);
     }
     static constexpr int frags(int kind) { return steps(kind) * tiles(kind) * 64; }
@@ -468,7 +490,9 @@ struct PrismFacCfg {
     // degree 2: the workgroups of a CU hide each other's gathers; degree 3 has
     // one per CU and prefetches
     static constexpr bool PIPE = P == 3;
-    static constexpr int WPE = P == 2 ? 3 : 2;
+    // (BF16X3 mass with three: 190.8 us against 189.3, FP32 mass with four 195
+    // against 189.5; diffusion takes what it needs)
+    static constexpr int WPE = P == 2 ? (FORM == F_MASS && BF ? 4 : 3) : 2;
     // accumulator slots of a wave: degree 2 the tiles of its two pairs, degree
     // 3 those of one pair b < b' or of two pairs b = b'
     static constexpr int TW = P == 2 ? tiles(0) + tiles(1) : 2 * tiles(1);
@@ -484,6 +508,8 @@ struct PrismFacCfg {
     static constexpr int PADV = P == 3 ? 16 / (int)sizeof(out_t) : 0;
     static constexpr int RS = NS + PADV, CS = NS * RS + PADV;
     static constexpr int ST_BYTES = PC * CS * (int)sizeof(out_t);
+    // degree 2: vertices and field values of a cell, in LDS (doubles; odd)
+    static constexpr int XS = 25;
     static constexpr int LDS_BYTES = ((G_BYTES > ST_BYTES ? G_BYTES : ST_BYTES) + 15) / 16 * 16;
     static_assert(LDS_BYTES + NQ * 32 <= 160 * 1024 && CB % 16 == 0, "LDS");
 };
@@ -542,7 +568,44 @@ __device__ __forceinline__ void prism_contract(const double* gt, const double* w
 #pragma unroll
         for (int t = 0; t < NT; ++t) b[t] = buffer_frag<frag_t>(rsrc, vo, (unsigned)(t * 64) * FB);
     };
-    if constexpr (C::BF) {
+    if constexpr (C::BF && T == 1) {
+        constexpr int KS = C::steps(KIND), NP = C::FULLB + C::REM;
+        frag_t b[2][NT], a[NC][KS];
+        load_b(b[0], 0);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            __bf16 x[NP][3];  // the parts of the coefficients at the points 4 m + g, then the leftover one
+#pragma unroll
+            for (int m = 0; m < NP; ++m) {
+                double cf[1];
+                prism_coefs<FORM, P, KIND>(row[c] + (m < C::FULLB ? 4 * m + g : C::NI - 1) * (M1 * JQ), w, cf);
+                const float v = (float)cf[0];
+                x[m][0] = (__bf16)v;
+                x[m][1] = (__bf16)(v - (float)x[m][0]);
+                x[m][2] = (__bf16)(v - (float)x[m][0] - (float)x[m][1]);
+            }
+#pragma unroll
+            for (int f = 0; f < 8 * KS; ++f) {
+                __bf16 v = (__bf16)0.0f;
+                if (f < 6 * C::FULLB) {
+                    v = x[f / 6][kMassParts[f % 6][0]];
+                } else if (f < 6 * C::FULLB + 2 * C::REM) {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+                        v = g == k ? x[NP - 1][kMassParts[kMassRest[k][f - 6 * C::FULLB]][0]] : v;
+                }
+                a[c][f / 8][f % 8] = v;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            if (s + 1 < KS) load_b(b[(s + 1) & 1], s + 1);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) acc[c][S0 + t] = mfma<PREC>(a[c][s], b[s & 1][t], acc[c][S0 + t]);
+        }
+    } else if constexpr (C::BF) {
         frag_t bh[NT], bl[NT];
         load_b(bh, 0);
         load_b(bl, 1);
@@ -559,15 +622,6 @@ __device__ __forceinline__ void prism_contract(const double* gt, const double* w
                     const float x = t < T && (C::REM == 0 || i < C::NI) ? (float)cf[t < T ? t : 0] : 0.0f;
                     ah[c][t] = (__bf16)x;
                     al[c][t] = (__bf16)(x - (float)ah[c][t]);
-                }
-                if constexpr (T == 1) {
-                    // mass: two of the unused slots take the third part of the
-                    // coefficient, against the table's value, and the
-                    // coefficient, against the third part of that
-                    const float x = C::REM == 0 || i < C::NI ? (float)cf[0] : 0.0f;
-                    ah[c][1] = (__bf16)(x - (float)ah[c][0] - (float)al[c][0]);
-                    ah[c][2] = ah[c][0];
-                    al[c][2] = al[c][0];
                 }
             }
 #pragma unroll
@@ -650,6 +704,7 @@ __attribute__((amdgpu_waves_per_eu(PrismFacCfg<FORM, P, FD, PREC>::WPE))) void k
                   CELLS = C::CELLS, NOFF = C::NOFF;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ double sq[NQ * 4];
+    __shared__ double sx[C::PIPE ? 1 : CELLS * C::XS];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double* gt = reinterpret_cast<double*>(lds);
@@ -725,10 +780,40 @@ __attribute__((amdgpu_waves_per_eu(PrismFacCfg<FORM, P, FD, PREC>::WPE))) void k
     for (; grp < ngroups; grp += GS) {
         const int64_t base = grp * CELLS;
         if constexpr (!C::PIPE) {
-            prism_idx<FD>(A, cell_of(grp), ix);
-            prism_raw<FD>(A, cell_of(grp), ix, raw);
+            // each vertex and each field value is read by one thread
+            static_assert(64 * C::WAVES / CELLS >= 12, "a thread per cell and value");
+            const int64_t cell = cell_of(grp);
+            double* x = sx + r * C::XS;
+            if (pg < (FD > 0 ? 12 : 6)) {
+                // vertex pg, or field value pg - 6: one code path, so that a
+                // wave with both does not wait for two chains of loads
+                const bool vert = FD == 0 || pg < 6;
+                int64_t at = cell * 6 + (vert ? pg : pg - 6);
+                const int32_t* map = vert ? A.c2v : A.f.map;
+                if (map) at = gload_nt(map + at);
+                const double* src = vert ? A.coords + at * 3 : A.f.values + at;
+                double v[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) v[i] = gload(src + (vert ? i : 0));
+                if (vert) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) x[pg * 3 + i] = v[i];
+                } else {
+                    x[12 + pg] = v[0];
+                }
+            }
         }
-        lds_barrier();  // the previous group's staging reads are done (and sq is loaded)
+        // the previous group's staging reads are done, sx (and sq) is written
+        lds_barrier();
+        if constexpr (!C::PIPE) {
+            const double* x = sx + r * C::XS;
+#pragma unroll
+            for (int v = 0; v < 6; ++v) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) raw.x[v][i] = x[v * 3 + i];
+                if constexpr (FD > 0) raw.f[v] = x[18 + v];
+            }
+        }
         // G: thread (cell r, triangle point pg) forms the points of that vertical line
         {
             const bool valid = base + r < A.ncells;
@@ -953,13 +1038,23 @@ void prism_fac_pack(const std::vector<ld> (&R)[2], int prec, std::vector<char>& 
                 for (int l = 0; l < 64; ++l) {
                     const int g = l / 16, u = 16 * t + l % 16;
                     if (C::BF) {
-                        // block s / 2 of four points, slot = type; hi, then lo
-                        for (int k = 0; k < 8; ++k) {
-                            const float x = (float)val(T == 1 && k < 3 ? 0 : k, 4 * (s / 2) + g, u);
+                        // parts of the value: hi, lo, third
+                        auto part = [&](int type, int i, int k) -> uint16_t {
+                            const float x = (float)val(type, i, u);
                             const uint16_t hi = bf16_bits_host(x), lo = bf16_bits_host(x - bf16_float_host(hi));
-                            uint16_t h = s % 2 == 0 ? hi : lo;
-                            if (T == 1 && k == 2)  // mass: the third part
-                                h = s % 2 == 0 ? bf16_bits_host(x - bf16_float_host(hi) - bf16_float_host(lo)) : 0;
+                            return k == 0 ? hi : (k == 1 ? lo : bf16_bits_host(x - bf16_float_host(hi) - bf16_float_host(lo)));
+                        };
+                        for (int k = 0; k < 8; ++k) {
+                            uint16_t h = 0;
+                            if (T == 1) {
+                                const int f = 8 * s + k, r = f - 6 * C::FULLB;
+                                if (r < 0) h = part(0, 4 * (f / 6) + g, dev::kMassParts[f % 6][1]);
+                                else if (r < 2 * C::REM && g < 3)
+                                    h = part(0, C::NI - 1, dev::kMassParts[dev::kMassRest[g][r]][1]);
+                            } else {
+                                // block s / 2 of four points, slot = type; hi, then lo
+                                h = part(k, 4 * (s / 2) + g, s % 2);
+                            }
                             put(&h, 2);
                         }
                     } else {

@@ -229,3 +229,21 @@ def test_prism_factored_ragged_counts(cf, oracle, form, p, field, prec):
         ref = oracle.assemble(form, sub, p, fields=fields, constants=cst)
         got = assemble_gpu(form, sub, p, fields, constants=cst, precision=prec).cpu().numpy()
         assert cell_rel_err(got, ref) < TOL[prec], count
+
+
+@pytest.mark.parametrize("field", [None, "map", "cellmajor"])
+@pytest.mark.parametrize("p", [2, 3])
+def test_prism_mass_bf16x3_as_accurate_as_fp32(cf, oracle, p, field):
+    """The mass form's BF16X3 product keeps three parts of both operands: the FP32 bar, at counts around the 16- and
+    32-cell tiles."""
+    from gpu_util import TOL, assemble_gpu, cell_rel_err
+    rng = np.random.default_rng(720 + p)
+    mesh = I.make_prism_mesh(4, 0.12, rng)
+    vals = rng.uniform(0.5, 1.5, (mesh.nvert, 1))
+    for count in (1, 16, 33):
+        sub = I.Mesh(3, 4, mesh.coords, np.ascontiguousarray(mesh.cells[:count]))
+        fields = [] if field is None else [I.Field(vals, sub.cells, 1, 1)] if field == "map" else \
+            [I.Field(np.ascontiguousarray(vals[sub.cells]), None, 1, 1)]
+        ref = oracle.assemble("mass", sub, p, fields=fields)
+        got = assemble_gpu("mass", sub, p, fields, precision="bf16x3").cpu().numpy()
+        assert cell_rel_err(got, ref) < TOL["fp32"], count
