@@ -21,6 +21,12 @@
 // (whole cells in order: row pieces of many cells at a time reached only 60%
 // of that write rate).
 //
+// Degree 1: four waves a workgroup, so that a small mesh reaches more CUs, and
+// a larger ring (bg_sizes). P1 tetrahedra, 383,997 cells, FP64 / FP32 / BF16X3:
+// 98 / 67 / 75 us (all terms in every block 105 / 67 / 82; eight waves and the
+// ring of degree 2 101 / 75 / 89); 1,293 cells 6.7 / 6.3 / 7.4 (11.0 / 7.5 /
+// 9.1; 9.5 / 8.8 / 10.1). P1 triangles, 524,285: 51 / 37 / 44 (51 / 42 / 44; 53 /
+// 39 / 45).
 // 663,552 P2 tetrahedra: 980 us in FP64, 555 in FP32, 565 in BF16X3, against
 // 1,694, 814 and 846 for all terms in every block; what is left is the write
 // of the tensors (4.78 GB in FP64).
@@ -48,8 +54,6 @@ __host__ __device__ constexpr BgSizes bg_sizes(int d, int p, int prec) {
     s.ks0 = prec == PREC_BF16X3 ? (4 * s.kr0 + 31) / 32 : (s.kr0 + 3) / 4;
     s.row0 = prec == PREC_BF16X3 ? s.ks0 * 32 + 8 : s.ks0 * 4 + 1;
     s.nt = (s.nn + 15) / 16;
-    // cells a 16-row tile touches: four whole ones of 4 blocks, at most three of 9
-    s.ring = s.nb == 4 ? 4 : 3;
     const int gsz = prec == PREC_F64 ? 8 : (prec == PREC_F32 ? 4 : 2);
     const int osz = prec == PREC_F64 ? 8 : 4;
     const int fsz = prec == PREC_F64 ? 8 : (prec == PREC_F32 ? 4 : 16);
@@ -60,12 +64,21 @@ __host__ __device__ constexpr BgSizes bg_sizes(int d, int p, int prec) {
     s.d_bytes = (16 * s.nn * osz + 15) / 16 * 16;
     // the ring; before the first tile its memory holds the D rows and the state
     const int g0 = (16 * s.row0 * gsz + 15) / 16 * 16, w = 16 * (s.n | 1) * 8;
-    s.ring_bytes = cmax(s.ring * s.cellv * osz, g0 + w);
-    s.ring_bytes = (s.ring_bytes + 15) / 16 * 16;
-    s.wave_bytes = s.e_bytes + s.d_bytes + s.ring_bytes;
     constexpr int L = 160 * 1024;
+    const int most = p == 1 ? 4 : 8;  // waves
+    // Cells: degree 2 those that a 16-row tile touches (four whole ones of 4
+    // blocks, at most three of 9). Cells of degree 1 are small (576 bytes in
+    // FP32 on tetrahedra): one or two at a time fill neither the lanes nor the
+    // lines of a store, so the ring takes all 16 of the unit where three
+    // workgroups still fit a CU, else nine, which leave as eight and eight.
+    for (int cells : {16, 9, s.nb == 4 ? 4 : 3}) {
+        s.ring = cells;
+        s.ring_bytes = (cmax(cells * s.cellv * osz, g0 + w) + 15) / 16 * 16;
+        s.wave_bytes = s.e_bytes + s.d_bytes + s.ring_bytes;
+        if (p == 1 && (cells == 9 || 3 * most * s.wave_bytes <= L)) break;
+    }
     const int fit = L / s.wave_bytes;
-    s.waves = fit < 8 ? fit : 8;
+    s.waves = fit < most ? fit : most;
     // D's reference fragments in registers: 160 of them at one wave per SIMD,
     // 80 at two, else through the caches
     const int rregs = s.nt * s.ks0 * (fsz / 4);
@@ -204,8 +217,18 @@ __device__ __forceinline__ void bg_prepare(const LinArgs& A, BgWave<D, P, PREC>&
     wave_sync();
 }
 
-// Row tile m: E products on top of D, into the cell ring; then the cells
-// completed by this tile leave as one contiguous store range.
+// The first cell that has not left the ring before row tile m: cells leave
+// when the next tile's would not fit beside them (and after the last tile).
+constexpr int bg_left(int nb, int ring, int m) {
+    int left = 0;
+    for (int t = 0; t < m; ++t)
+        if (t + 1 == nb || (16 * (t + 2) + nb - 1) / nb - left > ring) left = 16 * (t + 1) / nb;
+    return left;
+}
+
+// Row tile m: E products on top of D, into the cell ring; then, when the ring
+// has no room for the next tile's cells, the complete ones leave as one
+// contiguous store range.
 template <int D, int P, int PREC, bool FULL, int m>
 __device__ __forceinline__ void bg_rowtile(const LinArgs& A, const BgWave<D, P, PREC>& W, int64_t unit_base) {
     using C = BgCfg<D, P, PREC>;
@@ -255,14 +278,14 @@ __device__ __forceinline__ void bg_rowtile(const LinArgs& A, const BgWave<D, P, 
             for (int v = 0; v < 4; ++v) W.ring[base[v] + ea * N + eb] = (out_t)acc[v];
         }
     }
-    wave_sync();
-    // cells [cd0, cd1) of the unit are complete; their slots are consecutive
-    // except where the ring wraps (at chunk WQ of the range)
-    constexpr int cd0 = (16 * m) / NB, cd1 = (16 * (m + 1)) / NB;
+    // cells [cd0, cd1) of the unit leave; their slots are consecutive except
+    // where the ring wraps (at chunk WQ of the range)
+    constexpr int cd0 = bg_left(NB, C::RING, m), cd1 = bg_left(NB, C::RING, m + 1);
     constexpr int CPC = C::CPC, NQ = (cd1 - cd0) * CPC;
     constexpr int s0 = cd0 % C::RING, WQ = (C::RING - s0) * CPC, WRAP = C::RING * CPC;
     static_assert(cd1 - cd0 <= C::RING, "ring");
     if constexpr (NQ > 0) {
+        wave_sync();
         const vu32x4* rb = reinterpret_cast<const vu32x4*>(W.ring) + s0 * CPC;
         // a wave-uniform base and 32-bit byte offsets: scalar base addressing
         char* dst = reinterpret_cast<char*>(uniform_ptr(reinterpret_cast<vu32x4*>(A.out) +
@@ -279,8 +302,8 @@ __device__ __forceinline__ void bg_rowtile(const LinArgs& A, const BgWave<D, P, 
             if constexpr (!FULL) ok = ok && unit_base + cd0 + q / CPC < A.ncells;
             if (ok) gstore_nt(reinterpret_cast<vu32x4*>(dst + (uint32_t)(q * 16)), rb[li]);
         }
+        wave_sync();
     }
-    wave_sync();
 }
 
 template <int D, int P, int PREC, bool FULL, int m>

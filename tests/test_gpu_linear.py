@@ -354,3 +354,33 @@ def test_burgers_cell_rows(cf, oracle, d, p, q, prec):
         for g in (f, I.Field(np.ascontiguousarray(w.values[f.cell_to_dof]), None, f.degree, f.ncomp)):
             got = assemble_gpu("burgers", sub, p, [g], constants=cst, quad_degree=q, precision=prec).cpu().numpy()
             assert cell_rel_err(got, ref) < TOL[prec], (count, g.cell_to_dof is None)
+
+
+@pytest.mark.parametrize("mapped", [True, False])
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("d,p,count", [(2, 1, 300_005), (2, 2, 150_003), (3, 1, 150_011), (3, 2, 70_013)])
+def test_burgers_several_units_per_wave(cf, d, p, count, prec, mapped):
+    """More cells than two passes of the persistent grid take (256 CUs; 28, 16, 12 and 8 waves of 16 cells on each, the
+    most that the registers and the LDS of the four spaces allow), with a ragged end: equal bit for bit to calls on
+    parts of 8,000 cells, which leave every wave at most one unit."""
+    import torch
+    from gpu_util import to_dev
+    rng = np.random.default_rng(600 + 10 * d + p)
+    mesh = I.make_mesh(d, int(np.ceil((count / (2 if d == 2 else 6)) ** (1 / d))), 0.1, rng)
+    sub = I.Mesh(d, mesh.n, mesh.coords, np.ascontiguousarray(mesh.cells[:count]))
+    coords, c2v, _ = to_dev(sub, [])
+    dev, ns = c2v.device, I.n_scalar_dofs(d, p)
+    ndofs = count * ns // 5 + ns
+    dofs = (torch.arange(count * ns, device=dev) % ndofs).to(torch.int32).reshape(count, ns)
+    vals = torch.as_tensor(rng.uniform(-1, 1, (ndofs, d)), device=dev)
+    if not mapped:
+        vals = vals[dofs.long()].contiguous()
+
+    def call(a, b):
+        w = cf.DeviceField(vals, dofs[a:b].contiguous(), p, d) if mapped else cf.DeviceField(vals[a:b], None, p, d)
+        return cf.coffee_assemble("burgers", d, p, coords, c2v[a:b].contiguous(), coeffs=[w], constants=[0.7, 1.3],
+                                  precision=prec)
+
+    whole = call(0, count)
+    for a in range(0, count, 8000):
+        assert torch.equal(whole[a:a + 8000], call(a, min(a + 8000, count))), a
