@@ -90,27 +90,33 @@ __global__ __launch_bounds__(256) void k_zero(T* p, int64_t n) {
 // it sees about half as many, and lanes on consecutive addresses share a
 // request; one thread per tensor row, each searching its own matrix row and
 // adding on its own, made one request per entry and waited for every search
-// step. No search is left: a column costs one hash probe. (Summing into
-// copies of the matrix rows in LDS, with a binary search per entry, was bound
-// by the LDS reads of the search: 443 us in all for the case below.)
+// step. A column costs one hash probe, no search but in long rows. (Summing
+// into copies of the matrix rows in LDS, with a binary search per entry, was
+// bound by the LDS reads of the search: 443 us in all for the case below.)
 // Helmholtz P2 tetrahedra, FP64, 384,000 cells (assembly of the tensors
 // included): 1,597 -> 474 us, of which the adds themselves take 185.
-// Two workgroups of 16 waves fill a CU (77 KB of LDS each in FP64): the steps
-// of a run are short and wait for one another. Measured for the case above
-// and for elasticity P2 (41,154 cells): 512 threads and 81 rows 535 and
-// 491 us, 1,024 threads and 90 rows 474 and 448 us, 96 rows (one workgroup
-// per CU) 475 and 450 us.
+// Two workgroups of 16 waves fill a CU (71 KB of LDS each in FP64, 64 registers;
+// with 68 of them, one workgroup, elasticity on 82,941 P1 tetrahedra took 303
+// us instead of 258): the steps of a run are short and wait for one another.
+// Measured for the case above and for elasticity P2 (41,154 cells): 512 threads
+// and 81 rows 535 and 491 us, 1,024 threads and 90 rows 474 and 448 us, 96 rows
+// (one workgroup per CU) 475 and 450 us.
 constexpr int kCsrThreads = 1024;
 constexpr int kCsrDense = 90;   // rows of the LDS matrix
 constexpr int kCsrHash = 1024;  // more slots than a run has local dofs
 constexpr int kCsrAhead = 5;    // columns in flight per lane and row
+// A row with more columns is searched for the run's columns (at most 90)
+// instead of being read by every run that touches it: a fan of 100,000 P1
+// triangles around one vertex, whose row has a column for each, 3,460 us when
+// it is read, 63 when it is searched (10,000 triangles 129 and 20).
+constexpr int kCsrLong = 1024;
 
 // The element tensor is component-blocked ((c, a) -> c * n + a); the global
 // index of local dof (c, a) is dof(a) * NC + c. CELLS: cells per run, such
 // that a run of a mesh in spatial order has at most kCsrDense / NC dofs; a run
 // that has more is taken in parts of SAFE cells, which cannot.
 template <typename T, int NL, int NC, int CELLS>
-__global__ __launch_bounds__(kCsrThreads) void k_scatter_csr(const T* __restrict__ A, const int32_t* __restrict__ c2d,
+__global__ __launch_bounds__(kCsrThreads, 8) void k_scatter_csr(const T* __restrict__ A, const int32_t* __restrict__ c2d,
                                                             int64_t ncells, const int64_t* __restrict__ row_ptr,
                                                             const int32_t* __restrict__ col_idx,
                                                             T* __restrict__ values) {
@@ -121,7 +127,8 @@ __global__ __launch_bounds__(kCsrThreads) void k_scatter_csr(const T* __restrict
     __shared__ T dense[kCsrDense * kCsrDense];
     __shared__ int32_t hkey[kCsrHash];    // dof, or -1
     __shared__ uint8_t hnum[kCsrHash];    // its number
-    __shared__ int64_t ustart[UMAX * NC]; // matrix rows of the dofs by number
+    __shared__ int32_t udof[UMAX];        // dofs by number
+    __shared__ int64_t ustart[UMAX * NC]; // their matrix rows
     __shared__ int32_t ulen[UMAX * NC];
     __shared__ uint8_t lnum[CELLS * NL];  // local dof -> number
     __shared__ int nuniq;
@@ -162,6 +169,7 @@ __global__ __launch_bounds__(kCsrThreads) void k_scatter_csr(const T* __restrict
                 const int u = atomicAdd(&nuniq, 1);
                 if (u < UMAX) {
                     hnum[h] = (uint8_t)u;
+                    udof[u] = mydof;
 #pragma unroll
                     for (int c = 0; c < NC; ++c) {
                         const int64_t n1 = rp[c + 1] - rp[c];  // a row outside the pattern has none
@@ -181,15 +189,20 @@ __global__ __launch_bounds__(kCsrThreads) void k_scatter_csr(const T* __restrict
         const int W = nu * NC;  // rows and columns of the dense matrix
         if (tid < nd) lnum[tid] = hnum[h];
         for (int i = tid; i < W * W; i += kCsrThreads) dense[i] = T(0);
-        // first columns of this lane group's matrix rows
+        // first columns of this lane group's matrix rows (long rows: later)
         int64_t b0[RL];
         int len[RL];
+        bool more = false;
         int32_t x[RL][kCsrAhead];
 #pragma unroll
         for (int k = 0; k < RL; ++k) {
             const int r = (tid >> 4) + k * GROUPS;
             b0[k] = r < W ? ustart[r] : 0;
             len[k] = r < W ? ulen[r] : 0;
+            if (len[k] > kCsrLong) {
+                len[k] = 0;
+                more = true;
+            }
         }
 #pragma unroll
         for (int k = 0; k < RL; ++k)
@@ -228,7 +241,28 @@ __global__ __launch_bounds__(kCsrThreads) void k_scatter_csr(const T* __restrict
 #pragma unroll
             for (int j = 0; j < kCsrAhead; ++j)
                 if (lane + 16 * j < len[k]) add(r, b0[k] + lane + 16 * j, x[k][j]);
-            for (int64_t i = lane + 16 * kCsrAhead; i < len[k]; i += 16) add(r, b0[k] + i, col_idx[b0[k] + i]);
+            for (int i = lane + 16 * kCsrAhead; i < len[k]; i += 16) add(r, b0[k] + i, col_idx[b0[k] + i]);
+        }
+        if (more) {
+#pragma unroll 1
+            for (int r = tid >> 4; r < W; r += GROUPS) {
+                const int n = ulen[r];
+                const int64_t at = ustart[r];
+                if (n <= kCsrLong) continue;
+                // the run's columns, searched in the row
+                for (int j = lane; j < W; j += 16) {
+                    const T s = dense[r * W + j];
+                    if (s == T(0)) continue;
+                    const int32_t col = udof[j / NC] * NC + j % NC;
+                    int lo = 0, hi = n - 1;
+                    while (lo < hi) {  // first index with col_idx >= col
+                        const int mid = lo + (hi - lo) / 2;
+                        if (col_idx[at + mid] < col) lo = mid + 1;
+                        else hi = mid;
+                    }
+                    if (col_idx[at + lo] == col) atomicAdd(&values[at + lo], s);
+                }
+            }
         }
         __syncthreads();
         e0 += m;

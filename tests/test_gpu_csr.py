@@ -167,3 +167,33 @@ def test_csr_runs_of_scattered_cells(cf, oracle, form, d, p, n, prec):
         np.add.at(ref, np.searchsorted(keys, (g[:, :, None] * (nd * nc) + g[:, None, :]).ravel()), A.ravel())
         # entries are sums of at most a few dozen tensor values of that size
         assert np.abs(got - ref).max() <= 10 * TOL[prec] * np.abs(A).max(), count
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("form,cells", [("mass", 1021), ("mass", 1026), ("helmholtz", 5003), ("elasticity", 511),
+                                        ("elasticity", 2001)])
+def test_csr_long_rows(cf, oracle, form, cells, prec):
+    """A fan of triangles around one vertex: its matrix row has a column for every vertex (cells + 2, times two in
+    elasticity), below and above the length from which the run's columns are searched in a row, and the rest are
+    short."""
+    import torch
+    from gpu_util import TOL, to_dev
+    t = np.linspace(0, 1.5 * np.pi, cells + 1)
+    x = np.concatenate([np.zeros((1, 2)), np.stack([np.cos(t), np.sin(t)], 1)])
+    i = np.arange(cells)
+    mesh = I.Mesh(2, 1, x, np.stack([0 * i, i + 1, i + 2], 1).astype(np.int32))
+    cst = [1.5, 0.5] if form == "elasticity" else []
+    nc = 2 if form == "elasticity" else 1
+    ref = oracle.assemble_global(form, mesh, 1, mesh.cells, mesh.nvert, constants=cst)
+    coords, c2v, _ = to_dev(mesh, [])
+    row_ptr, col_idx = cf.coffee_csr_pattern(c2v, mesh.nvert, nc)
+    assert int(row_ptr[1]) == nc * (cells + 2)
+    np.testing.assert_array_equal(col_idx.cpu().numpy(), ref.indices)
+    vals = cf.coffee_assemble_csr(form, 2, 1, coords, c2v, row_ptr, col_idx, mesh.nvert, constants=cst, precision=prec)
+    torch.cuda.synchronize()
+    got = vals.cpu().numpy()
+    # the hub's diagonal sums `cells` entries of one sign, in runs: rounding grows with the number of sums
+    scale = np.abs(ref.data).max()
+    assert np.abs(got - ref.data).max() <= 4 * TOL[prec] * scale
+    short = np.repeat(np.diff(ref.indptr), np.diff(ref.indptr)) <= 1024
+    assert np.abs(got - ref.data)[short].max() <= 4 * TOL[prec] * np.abs(ref.data[short]).max()
