@@ -111,16 +111,22 @@ constexpr int kCsrAhead = 5;    // columns in flight per lane and row
 // it is read, 63 when it is searched (10,000 triangles 129 and 20).
 constexpr int kCsrLong = 1024;
 
+// Cells that fit the LDS matrix in any order, at most the cells of a run.
+constexpr int csr_safe(int nl, int nc, int cells) {
+    return kCsrDense / nc / nl < cells ? kCsrDense / nc / nl : cells;
+}
+
 // The element tensor is component-blocked ((c, a) -> c * n + a); the global
 // index of local dof (c, a) is dof(a) * NC + c. CELLS: cells per run, such
 // that a run of a mesh in spatial order has at most kCsrDense / NC dofs; a run
-// that has more is taken in parts of SAFE cells, which cannot.
+// that has more is taken in parts of SAFE cells, which cannot. (CELLS as an
+// argument of the kernel: elasticity on P1 and P2 triangles 3% slower.)
 template <typename T, int NL, int NC, int CELLS>
 __global__ __launch_bounds__(kCsrThreads, 8) void k_scatter_csr(const T* __restrict__ A, const int32_t* __restrict__ c2d,
                                                             int64_t ncells, const int64_t* __restrict__ row_ptr,
                                                             const int32_t* __restrict__ col_idx,
                                                             T* __restrict__ values) {
-    constexpr int N = NL * NC, UMAX = kCsrDense / NC, SAFE = UMAX / NL < CELLS ? UMAX / NL : CELLS;
+    constexpr int N = NL * NC, UMAX = kCsrDense / NC, SAFE = csr_safe(NL, NC, CELLS);
     static_assert(SAFE >= 1 && CELLS * NL <= kCsrThreads && 2 * CELLS * NL <= kCsrHash, "run too long");
     constexpr int PL = (CELLS * N * NL + kCsrThreads - 1) / kCsrThreads;        // entry groups of a thread
     constexpr int GROUPS = kCsrThreads / 16, RL = (kCsrDense + GROUPS - 1) / GROUPS;  // rows of a lane group
@@ -396,11 +402,30 @@ namespace {
 constexpr int64_t kCsrChunk = 1 << 17;
 
 template <typename T, int NL, int NC, int CELLS>
-bool scatter_launch(const T* A, const int32_t* map, int64_t ncells, const int64_t* row_ptr, const int32_t* col_idx,
-                    T* values, hipStream_t s) {
+void scatter_runs(const T* A, const int32_t* map, int64_t ncells, const int64_t* row_ptr, const int32_t* col_idx,
+                  T* values, hipStream_t s) {
     const int64_t runs = (ncells + CELLS - 1) / CELLS;
     hipLaunchKernelGGL((dev::k_scatter_csr<T, NL, NC, CELLS>), dim3((unsigned)((runs + 7) / 8 * 8)),
                        dim3(dev::kCsrThreads), 0, s, A, map, ncells, row_ptr, col_idx, values);
+}
+
+// Runs of SAFE cells, which fit the LDS matrix in any order of the cells, where
+// all of them are resident at once (two workgroups per CU): such a mesh has too
+// few long runs for the CUs, and a long run of scattered cells is taken in
+// parts, one after the other. Helmholtz P1 tetrahedra FP64, the whole call in
+// a graph, long runs / SAFE, us: cells in mesh order 1,293 10.0 / 9.0, 10,365
+// (471 runs) 10.8 / 10.3, 24,573 (1,117 runs) 12.6 / 15.7; in random order
+// 1,293 21.6 / 10.1, 10,365 24.7 / 13.5, 24,573 28.2 / 22.5.
+template <typename T, int NL, int NC, int CELLS>
+bool scatter_launch(const T* A, const int32_t* map, int64_t ncells, const int64_t* row_ptr, const int32_t* col_idx,
+                    T* values, hipStream_t s) {
+    constexpr int SAFE = dev::csr_safe(NL, NC, CELLS);
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return false;
+    if (ncells <= (int64_t)SAFE * 2 * num_cu(device))
+        scatter_runs<T, NL, NC, SAFE>(A, map, ncells, row_ptr, col_idx, values, s);
+    else
+        scatter_runs<T, NL, NC, CELLS>(A, map, ncells, row_ptr, col_idx, values, s);
     return true;
 }
 

@@ -197,3 +197,53 @@ def test_csr_long_rows(cf, oracle, form, cells, prec):
     assert np.abs(got - ref.data).max() <= 4 * TOL[prec] * scale
     short = np.repeat(np.diff(ref.indptr), np.diff(ref.indptr)) <= 1024
     assert np.abs(got - ref.data)[short].max() <= 4 * TOL[prec] * np.abs(ref.data[short]).max()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("shuffled", [False, True])
+@pytest.mark.parametrize("form,cell,p", [
+    ("mass", "triangle", 1), ("mass", "triangle", 2), ("mass", "triangle", 3), ("mass", "triangle", 4),
+    ("elasticity", "triangle", 1), ("elasticity", "triangle", 2), ("elasticity", "triangle", 3),
+    ("mass", "tetrahedron", 1), ("mass", "tetrahedron", 2), ("mass", "tetrahedron", 3), ("mass", "tetrahedron", 4),
+    ("elasticity", "tetrahedron", 1), ("elasticity", "tetrahedron", 2), ("elasticity", "tetrahedron", 3),
+    ("mass", "prism", 1), ("mass", "prism", 2)])
+def test_csr_long_and_short_runs(cf, oracle, form, cell, p, shuffled, prec):
+    """Every space, at the largest count that takes the runs that always fit (90 dof rows, two workgroups per CU) and
+    a few cells more, which take the long ones: cells in mesh order, and in random order (long runs are split)."""
+    import torch
+    from gpu_util import TOL, to_dev
+    d = 2 if cell == "triangle" else 3
+    nc = d if form == "elasticity" else 1
+    nl = {"triangle": (p + 1) * (p + 2) // 2, "tetrahedron": (p + 1) * (p + 2) * (p + 3) // 6,
+          "prism": (p + 1) * (p + 2) // 2 * (p + 1)}[cell]
+    most = 90 // nc // nl * 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(800 + 10 * d + p)
+    n = int(np.ceil(((most + 5) / {"triangle": 2, "tetrahedron": 6, "prism": 2}[cell]) ** (1 / d)))
+    mesh = I.make_prism_mesh(n, 0.1, rng) if cell == "prism" else I.make_mesh(d, n, 0.1, rng)
+    if p == 1:
+        c2d, nd = mesh.cells, mesh.nvert
+    elif p == 2 and cell != "prism":
+        c2d, nd = I.p2_dofmap(mesh.cells, mesh.n, d)
+    else:  # distinct dofs per cell, shared by neighbours in number: any map is a valid space for the scatter
+        nd = mesh.ncells * nl // 5 + 2 * nl
+        c2d = (np.arange(mesh.ncells)[:, None] * (nl // 5 + 1) + np.arange(nl)[None, :]) % nd
+    order = rng.permutation(mesh.ncells) if shuffled else np.arange(mesh.ncells)
+    cells = np.ascontiguousarray(mesh.cells[order])
+    c2d = np.ascontiguousarray(np.asarray(c2d, dtype=np.int32)[order])
+    cst = [1.5, 0.5] if form == "elasticity" else []
+    coords, c2v, _ = to_dev(I.Mesh(d, n, mesh.coords, cells), [])
+    code = {"triangle": 2, "tetrahedron": 3, "prism": 6}[cell]
+    dofs = torch.as_tensor(c2d, device=coords.device)
+    row_ptr, col_idx = cf.coffee_csr_pattern(dofs, nd, nc)
+    rp, ci = row_ptr.cpu().numpy(), col_idx.cpu().numpy()
+    A = oracle.assemble(form, I.Mesh(d, n, mesh.coords, np.ascontiguousarray(cells[:most + 5])), p, constants=cst)
+    keys = np.repeat(np.arange(nd * nc), np.diff(rp)) * (nd * nc) + ci
+    g = np.concatenate([c2d[:most + 5].astype(np.int64) * nc + c for c in range(nc)], axis=1)
+    for count in (most, most + 5):
+        got = cf.coffee_assemble_csr(form, code, p, coords, c2v[:count].contiguous(), row_ptr, col_idx, nd,
+                                     cell_to_dof=dofs[:count].contiguous(), constants=cst, precision=prec).cpu().numpy()
+        ref = np.zeros(len(ci))
+        at = np.searchsorted(keys, (g[:count, :, None] * (nd * nc) + g[:count, None, :]).ravel())
+        np.add.at(ref, at, A[:count].ravel())
+        # entries are sums of at most a few dozen tensor values of that size
+        assert np.abs(got - ref).max() <= 10 * TOL[prec] * np.abs(A).max(), count
