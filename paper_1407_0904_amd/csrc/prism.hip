@@ -415,7 +415,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // are its k's of the steps (ib, type): the G operand of a product never passes
 // through LDS. A ninth point (degree 2) is spread over the four lane groups
 // type by type. The R fragments, shared by every pair of a kind, are raw
-// buffer loads, one step ahead. Then, in passes of as many cells as the LDS
+// buffer loads, one step ahead (BF16X3: a block's at its start). Then, in passes of as many cells as the LDS
 // holds, the waves write their accumulators (both mirrored entries) into a
 // staging area over the G values, and the workgroup copies whole cells out as
 // 16-byte stores (a matrix written a few entries at a time leaves partial
@@ -434,10 +434,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 //   mass, field     BF16X3       194              261          195
 //   diffusion       FP64         667              497          490
 //   diffusion       FP32         376              301          299
-//   diffusion       BF16X3       267              278          269
+//   diffusion       BF16X3       264              276          264
 // (the BF16X3 mass form also packs its products: kMassParts). 65,536 P3
-// prisms: diffusion FP64 765 -> 367, FP32 415 -> 217, BF16X3 215 -> 175; mass
-// BF16X3 108 -> 129 with one product per slot, 101 packed.
+// prisms: diffusion FP64 765 -> 367, FP32 415 -> 217, BF16X3 222 -> 175; mass
+// BF16X3 109 -> 128 with one product per slot, 101 packed.
 
 // Workgroup barrier that orders LDS accesses only. Nothing passes between the
 // threads through global memory, and __syncthreads would also wait until
@@ -607,11 +607,13 @@ __device__ __forceinline__ void prism_contract(const double* gt, const double* w
         }
     } else if constexpr (C::BF) {
         frag_t bh[NT], bl[NT];
-        load_b(bh, 0);
-        load_b(bl, 1);
 #pragma unroll 1
         for (int ib = 0; ib < (C::NI + 3) / 4; ++ib) {
             frag_t ah[NC], al[NC];
+            // in flight while the coefficients are formed (a block ahead, held
+            // over the products: diffusion P2 268 us against 264)
+            load_b(bh, 2 * ib);
+            load_b(bl, 2 * ib + 1);
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const int i = 4 * ib + g;
@@ -636,9 +638,6 @@ __device__ __forceinline__ void prism_contract(const double* gt, const double* w
                     // it 2.3e-6; over points and terms, without it, 2.6e-6
                     acc[c][S0 + t] = mfma<PREC>(al[c], bl[t], acc[c][S0 + t]);
                 }
-            const int nb = ib + 1 < (C::NI + 3) / 4 ? ib + 1 : ib;
-            load_b(bh, 2 * nb);
-            load_b(bl, 2 * nb + 1);
         }
     } else {
         constexpr int KS = C::steps(KIND);
