@@ -94,7 +94,8 @@ typedef enum {
                           tangent in FP64 and accumulates the element matrix in FP32.           */
     COFFEE_BF16X3 = 2  /* FP64 geometry; each contraction operand x split as x_hi = bf16(x),
                           x_lo = bf16(x - x_hi); hi*hi + hi*lo + lo*hi on bf16 MFMA with FP32
-                          accumulation; FP32 output                                             */
+                          accumulation (prisms of degree 2 and 3 add lo*lo, their mass form a
+                          third part of each operand as well); FP32 output                      */
 } coffee_precision;
 
 /* Quadrature rule families. A quad_degree argument is q (collapsed

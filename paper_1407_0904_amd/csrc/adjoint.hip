@@ -49,15 +49,13 @@ struct AdjDirs {
     static constexpr int NF = nfield(D, FD);
     static constexpr int WC = (FORM == F_BURG) ? D : 1;
     static constexpr int N0 = FD > 0 ? NF * WC : 0;                      // field 0 dofs
-    static constexpr int N1 = (FORM == F_ELAST && FD > 0) ? NF : 0;      // field 1 dofs
 };
 
 // Accumulate the contribution of block B: value, Kbar and coefficient bars.
 template <int FORM, int D, int P, int FD, int B>
 __device__ inline void adjoint_block(const AdjArgs& A, const double* Rs, const CellData<FORM, D, FD, double>& cd,
                                      const double* lam_e,
-                                     const double* u_e, double& S, double (&Kbar)[D][D], double* f0bar,
-                                     double* f1bar) {
+                                     const double* u_e, double& S, double (&Kbar)[D][D], double* f0bar) {
     constexpr int NS = nsc(D, P), NN = NS * NS;
     constexpr int NC = ncomp_space(FORM, D);
     constexpr int C1 = B / NC, C2 = B % NC;
@@ -84,7 +82,7 @@ __device__ inline void adjoint_block(const AdjArgs& A, const double* Rs, const C
         }
         return t;
     };
-    reverse_G<FORM, D, FD, C1, C2>(cd, A.L, gbar, S, Kbar, f0bar, f1bar);
+    reverse_G<FORM, D, FD, C1, C2>(cd, A.L, gbar, S, Kbar, f0bar);
 }
 
 // One block per iteration of a runtime loop, so that the compiler keeps one
@@ -92,21 +90,20 @@ __device__ inline void adjoint_block(const AdjArgs& A, const double* Rs, const C
 template <int FORM, int D, int P, int FD, int B, int NB>
 __device__ inline void adjoint_block_switch(int b, const AdjArgs& A, const double* Rs,
                                             const CellData<FORM, D, FD, double>& cd, const double* lam,
-                                            const double* u, double& S, double (&Kbar)[D][D], double* f0bar,
-                                            double* f1bar) {
+                                            const double* u, double& S, double (&Kbar)[D][D], double* f0bar) {
     if constexpr (B < NB) {
-        if (b == B) adjoint_block<FORM, D, P, FD, B>(A, Rs, cd, lam, u, S, Kbar, f0bar, f1bar);
-        else adjoint_block_switch<FORM, D, P, FD, B + 1, NB>(b, A, Rs, cd, lam, u, S, Kbar, f0bar, f1bar);
+        if (b == B) adjoint_block<FORM, D, P, FD, B>(A, Rs, cd, lam, u, S, Kbar, f0bar);
+        else adjoint_block_switch<FORM, D, P, FD, B + 1, NB>(b, A, Rs, cd, lam, u, S, Kbar, f0bar);
     }
 }
 
 template <int FORM, int D, int P, int FD, int NB>
 __device__ inline void adjoint_blocks(const AdjArgs& A, const double* Rs, const CellData<FORM, D, FD, double>& cd,
                                       const double* lam, const double* u, double& S, double (&Kbar)[D][D],
-                                      double* f0bar, double* f1bar) {
+                                      double* f0bar) {
 #pragma unroll 1
     for (int b = 0; b < NB; ++b)
-        adjoint_block_switch<FORM, D, P, FD, 0, NB>(b, A, Rs, cd, lam, u, S, Kbar, f0bar, f1bar);
+        adjoint_block_switch<FORM, D, P, FD, 0, NB>(b, A, Rs, cd, lam, u, S, Kbar, f0bar);
 }
 
 // Reference tensors of the adjoint kernels live in LDS when they fit.
@@ -131,11 +128,11 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
         Rs = sR;
     }
     // per-wave combining of the gradient scatter-adds (vertex coordinates and
-    // the fields' dofs)
+    // the field's dofs)
     constexpr int TS = 128;
     constexpr int W0 = Dirs::N0 > 0 ? Dirs::WC : 1;
-    __shared__ unsigned long long ckx[4][TS], ck0[4][TS], ck1[4][TS];
-    __shared__ double cvx[4][TS * D], cv0[4][TS * W0], cv1[4][TS];
+    __shared__ unsigned long long ckx[4][TS], ck0[4][TS];
+    __shared__ double cvx[4][TS * D], cv0[4][TS * W0];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // wave-uniform loop: every lane takes part in the tables' clear and flush
     for (int64_t wbase = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) - lane; wbase < A.L.ncells;
@@ -146,7 +143,6 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
         if (!det) {
             combine_clear<D, TS>(ckx[wave], cvx[wave], lane);
             if constexpr (Dirs::N0 > 0) combine_clear<W0, TS>(ck0[wave], cv0[wave], lane);
-            if constexpr (Dirs::N1 > 0) combine_clear<1, TS>(ck1[wave], cv1[wave], lane);
             wave_sync();
         }
         CellIdx<FORM, D, FD> ix;
@@ -158,16 +154,14 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
         const double* lam = A.lam + cell * N;
         const double* u = A.u + cell * N;
         double S = 0.0, Kbar[D][D];
-        double f0bar[Dirs::N0 > 0 ? Dirs::N0 : 1], f1bar[Dirs::N1 > 0 ? Dirs::N1 : 1];
+        double f0bar[Dirs::N0 > 0 ? Dirs::N0 : 1];
 #pragma unroll
         for (int i = 0; i < D; ++i)
 #pragma unroll
             for (int j = 0; j < D; ++j) Kbar[i][j] = 0.0;
 #pragma unroll
         for (int r = 0; r < (Dirs::N0 > 0 ? Dirs::N0 : 1); ++r) f0bar[r] = 0.0;
-#pragma unroll
-        for (int r = 0; r < (Dirs::N1 > 0 ? Dirs::N1 : 1); ++r) f1bar[r] = 0.0;
-        adjoint_blocks<FORM, D, P, FD, NC * NC>(A, Rs, cd, lam, u, S, Kbar, f0bar, f1bar);
+        adjoint_blocks<FORM, D, P, FD, NC * NC>(A, Rs, cd, lam, u, S, Kbar, f0bar);
         if (A.cell_value && valid) A.cell_value[cell] = S;
 
         // chain to the coordinates
@@ -208,10 +202,6 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
 #pragma unroll
                     for (int r = 0; r < Dirs::N0; ++r) A.det_f0[cell * Dirs::N0 + r] = sd * f0bar[r];
                 }
-                if constexpr (Dirs::N1 > 0) {
-#pragma unroll
-                    for (int r = 0; r < Dirs::N1; ++r) A.det_f1[cell * Dirs::N1 + r] = sd * f1bar[r];
-                }
             } else {
                 if (A.grad_coords) {
 #pragma unroll
@@ -231,17 +221,6 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
                         }
                     }
                 }
-                if constexpr (Dirs::N1 > 0) {
-                    if (A.grad_f1) {
-                        constexpr int NF = Dirs::NF;
-#pragma unroll
-                        for (int r = 0; r < NF; ++r) {
-                            const int64_t key = A.L.f1.map ? (int64_t)ix.f1[r] : cell * NF + r;
-                            const double v = sd * f1bar[r];
-                            combine_add<1, TS>(ck1[wave], cv1[wave], (unsigned long long)key, &v, A.grad_f1);
-                        }
-                    }
-                }
             }
         }
         if (!det) {
@@ -249,9 +228,6 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
             if (A.grad_coords) combine_flush<D, TS>(ckx[wave], cvx[wave], A.grad_coords, lane);
             if constexpr (Dirs::N0 > 0) {
                 if (A.grad_f0) combine_flush<W0, TS>(ck0[wave], cv0[wave], A.grad_f0, lane);
-            }
-            if constexpr (Dirs::N1 > 0) {
-                if (A.grad_f1) combine_flush<1, TS>(ck1[wave], cv1[wave], A.grad_f1, lane);
             }
             wave_sync();
         }

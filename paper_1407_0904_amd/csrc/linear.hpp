@@ -411,7 +411,8 @@ __host__ __device__ inline void build_G(const CellData<FORM, D, FD, T>& cd, cons
 // exactly one factor |det J|, so dS/d|det J| = S / |det J| follows from S.
 template <int FORM, int D, int FD, int C1, int C2, typename GB>
 __host__ __device__ inline void reverse_G(const CellData<FORM, D, FD>& cd, const LinArgs& A, GB&& gbar, double& S,
-                                          double (&Kbar)[D][D], double* f0bar, double* f1bar) {
+                                          double (&Kbar)[D][D], double* f0bar) {
+    static_assert(FORM != F_ELAST, "elasticity has a kernel of its own");
     constexpr int NF = nfield(D, FD);
     const auto& K = cd.g.K;
     const double ad = cd.g.adet;
@@ -451,44 +452,6 @@ __host__ __device__ inline void reverse_G(const CellData<FORM, D, FD>& cd, const
                 S += g * cd.f0[r];
             } else {
                 S += g;
-            }
-        }
-    } else if constexpr (FORM == F_ELAST) {
-#pragma unroll
-        for (int r = 0; r < NF; ++r) {
-            const double mu = (FD > 0) ? cd.f0[r] : A.c0;
-            const double lm = (FD > 0) ? cd.f1[r] : A.c1;
-            double mubar = 0.0, lmbar = 0.0;
-#pragma unroll
-            for (int a = 0; a < D; ++a)
-#pragma unroll
-                for (int b = 0; b < D; ++b) {
-                    // G = ad (mu (delta KK^T_ab + K[a][C2] K[b][C1]) + lm K[a][C1] K[b][C2])
-                    const double gb = ad * gbar(t++);
-                    double kk = 0.0;
-                    if constexpr (C1 == C2) {
-#pragma unroll
-                        for (int i = 0; i < D; ++i) kk += K[a][i] * K[b][i];
-                    }
-                    mubar += gb * (kk + K[a][C2] * K[b][C1]);
-                    lmbar += gb * K[a][C1] * K[b][C2];
-                    const double gm = gb * mu, gl = gb * lm;
-                    if constexpr (C1 == C2) {
-#pragma unroll
-                        for (int i = 0; i < D; ++i) {
-                            Kbar[a][i] += gm * K[b][i];
-                            Kbar[b][i] += gm * K[a][i];
-                        }
-                    }
-                    Kbar[a][C2] += gm * K[b][C1];
-                    Kbar[b][C1] += gm * K[a][C2];
-                    Kbar[a][C1] += gl * K[b][C2];
-                    Kbar[b][C2] += gl * K[a][C1];
-                }
-            S += mu * mubar + lm * lmbar;
-            if constexpr (FD > 0) {
-                f0bar[r] += mubar;
-                f1bar[r] += lmbar;
             }
         }
     } else if constexpr (FORM == F_BURG) {

@@ -62,16 +62,8 @@ struct SvkArgs {
     double* det_u;       // [E][NS][D]
 };
 
-// Reference-table read: through the scalar path when the address is the same
-// in every lane (SC), else a plain (LDS) read.
-template <bool SC>
-__device__ inline double tread(const double* p) {
-    if constexpr (SC) return cload(p);
-    else return *p;
-}
-
 // F = I + U K at point q from the reference displacement gradient.
-template <int D, int NS, bool SC = false>
+template <int D, int NS>
 __device__ inline void svk_F(const double (&uv)[NS * D], const double (&K)[D][D], const double* dphi_q, int nq,
                              double (&F)[D][D]) {
     double U[D][D];  // U[i][a] = sum_r u_{r,i} dphi_r/dX_a
@@ -81,7 +73,7 @@ __device__ inline void svk_F(const double (&uv)[NS * D], const double (&K)[D][D]
         for (int a = 0; a < D; ++a) {
             double s = 0.0;
 #pragma unroll
-            for (int r = 0; r < NS; ++r) s += uv[r * D + i] * tread<SC>(dphi_q + (size_t)a * nq * NS + r);
+            for (int r = 0; r < NS; ++r) s += uv[r * D + i] * dphi_q[(size_t)a * nq * NS + r];
             U[i][a] = s;
         }
 #pragma unroll
@@ -932,21 +924,19 @@ __global__ __launch_bounds__(256, 2) void k_svk_jac(SvkArgs A) {
 // blocks have 36 entries, stay with the point kernel (62 us against 97).
 //
 // Work layout: a wave takes CPW consecutive cells; lane (cell, block c <= c',
-// half). Tetrahedra split a block's columns in halves {v0, v1, e01, e02, e13}
-// and its image under the vertex permutation 0 -> 2, 1 -> 3, 2 -> 1, 3 -> 0, so
-// that both halves run the same code on permuted data (50 accumulators each;
-// triangles keep the 36 of a block in one lane). The cell's lanes load its
-// dofs, form m_c = K K^T (reference gradient of u_c) and k_c = K e_c + m_c
-// at the vertices, F_c . F_c' and the K S K^T coefficients together in LDS; the whole
-// tensors are staged over that and leave as one contiguous range of 16-byte
-// stores. The next group's gathers are in flight meanwhile.
-template <int D>
+// half). A block's columns are split in halves {v0, v1, e01, e02, e13} and its
+// image under the vertex permutation 0 -> 2, 1 -> 3, 2 -> 1, 3 -> 0, so that
+// both halves run the same code on permuted data (50 accumulators each). The
+// cell's lanes load its dofs, form m_c = K K^T (reference gradient of u_c) and
+// k_c = K e_c + m_c at the vertices, F_c . F_c' and the K S K^T coefficients
+// together in LDS; the whole tensors are staged over that and leave as one
+// contiguous range of 16-byte stores. The next group's gathers are in flight
+// meanwhile.
 struct SvkJ2 {
-    static constexpr int V = D + 1, NS = nsc(D, 2), N = D * NS, NB = D * (D + 1) / 2;
-    static constexpr int SPLIT = D == 3 ? 2 : 1;
-    static constexpr int LPC = NB * SPLIT, CPW = 64 / LPC;
+    static constexpr int D = 3, V = D + 1, NS = nsc(D, 2), N = D * NS, NB = D * (D + 1) / 2;
+    static constexpr int LPC = 2 * NB, CPW = 64 / LPC;
     static constexpr int NP = V * (V + 1) / 2;       // pairs n <= l, also i <= j
-    static constexpr int NCOL = D == 3 ? 5 : NS;     // columns per lane
+    static constexpr int NCOL = NS / 2;              // columns per lane
     static constexpr int RL = (NS + LPC - 1) / LPC;  // dofs a lane loads
     // LDS of one cell, in doubles
     static constexpr int X = 0, U = X + V * D, MM = U + NS * D, GG = MM + D * V * V, HH = GG + D * V * D,
@@ -954,7 +944,6 @@ struct SvkJ2 {
                          CELL = (PH + NB * NP) | 1;
     // column of the lane's half for (j, q), -1 if it is not one of them
     static constexpr int col(int j, int q) {
-        if (D == 2) return j == q ? j : edge_dof<2>(j, q);
         const int lo = j < q ? j : q, hi = j < q ? q : j;
         if (lo == hi) return lo < 2 ? lo : -1;
         return lo == 0 && hi == 1 ? 2 : (lo == 0 && hi == 2 ? 3 : (lo == 1 && hi == 3 ? 4 : -1));
@@ -987,13 +976,13 @@ __device__ inline int pair_rt(int a, int b) {
     return lo * V - lo * (lo - 1) / 2 + hi - lo;
 }
 
-template <int D, typename OT>
+template <typename OT>
 __global__ __launch_bounds__(256, 1) void k_svk_jac2(SvkArgs A) {
-    using C = SvkJ2<D>;
-    constexpr int V = C::V, NS = C::NS, N = C::N, NB = C::NB, LPC = C::LPC, CPW = C::CPW, NP = C::NP, RL = C::RL;
+    using C = SvkJ2;
+    constexpr int D = C::D, V = C::V, NS = C::NS, N = C::N, NB = C::NB, LPC = C::LPC, CPW = C::CPW, NP = C::NP, RL = C::RL;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    double* wl = reinterpret_cast<double*>(lds + wave * C::template wave_bytes<OT>());
+    double* wl = reinterpret_cast<double*>(lds + wave * C::wave_bytes<OT>());
     const int cl = lane / LPC < CPW ? lane / LPC : CPW - 1, k = lane % LPC;
     const bool owner = lane < CPW * LPC;
     double* cc = wl + cl * C::CELL;
@@ -1097,7 +1086,7 @@ __global__ __launch_bounds__(256, 1) void k_svk_jac2(SvkArgs A) {
                 for (int i = 0; i < D; ++i) x[v][i] = cc[C::X + v * D + i];
             geometry_from_coords<D>(x, g);
         }
-        const double scale = g.adet * (D == 2 ? 16.0 / 720.0 : 16.0 / 5040.0);  // 16 |det J| / (D + 4)!
+        const double scale = g.adet * (16.0 / 5040.0);  // 16 |det J| / (D + 4)!
         if (owner && k < D) {
             // component k: reference gradient (GG), physical gradient (HH) and
             // m = K K^T (reference gradient) in barycentric components (MM) at the vertices
@@ -1425,17 +1414,17 @@ namespace {
 
 constexpr int svk_jac_slices(int, int p) { return p == 2 ? 2 : 1; }
 
-template <int D, typename OT>
+template <typename OT>
 hipError_t launch_jac2(const dev::SvkArgs& a, hipStream_t s, int ncu) {
-    using C = dev::SvkJ2<D>;
-    constexpr int lds = 4 * C::template wave_bytes<OT>();
+    using C = dev::SvkJ2;
+    constexpr int lds = 4 * C::wave_bytes<OT>();
     static_assert(lds <= 160 * 1024, "LDS");
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&dev::k_svk_jac2<D, OT>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&dev::k_svk_jac2<OT>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     const int64_t groups = (a.ncells + C::CPW - 1) / C::CPW;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((groups + 3) / 4, (int64_t)ncu * kJac2Grid));
-    hipLaunchKernelGGL((dev::k_svk_jac2<D, OT>), dim3(grid), dim3(256), lds, s, a);
+    hipLaunchKernelGGL((dev::k_svk_jac2<OT>), dim3(grid), dim3(256), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1475,7 +1464,7 @@ hipError_t launch_svk(int form, int precision, const dev::SvkArgs& a, hipStream_
         else hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 1, float>), dim3(grid), dim3(256), 0, s, a);
     } else {
         if constexpr (P == 2 && D == 3)
-            return f64 ? launch_jac2<D, double>(a, s, ncu) : launch_jac2<D, float>(a, s, ncu);
+            return f64 ? launch_jac2<double>(a, s, ncu) : launch_jac2<float>(a, s, ncu);
         constexpr int AH = svk_jac_slices(D, P);
         constexpr int CPW = 64 / (D * (D + 1) / 2 * AH);
         const int64_t waves = (a.ncells + CPW - 1) / CPW;
