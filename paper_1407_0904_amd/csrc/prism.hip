@@ -44,6 +44,8 @@ namespace coffee {
 namespace dev {
 
 typedef unsigned int u32x4p __attribute__((ext_vector_type(4)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
 
 constexpr int prism_ns(int p) { return (p + 1) * (p + 2) / 2 * (p + 1); }
 // G entries per point: the six pairs al <= be, then the mass term
@@ -434,7 +436,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 //   mass, field     BF16X3       194              261          195
 //   diffusion       FP64         667              497          490
 //   diffusion       FP32         376              301          299
-//   diffusion       BF16X3       264              276          264
+//   diffusion       BF16X3       258              269          254
 // (the BF16X3 mass form also packs its products: kMassParts). 65,536 P3
 // prisms: diffusion FP64 765 -> 367, FP32 415 -> 217, BF16X3 222 -> 175; mass
 // BF16X3 109 -> 128 with one product per slot, 101 packed.
@@ -616,14 +618,20 @@ __device__ __forceinline__ void prism_contract(const double* gt, const double* w
             load_b(bl, 2 * ib + 1);
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
+                // points that do not exist take another's coefficients, against zeros in the table
                 const int i = 4 * ib + g;
                 double cf[T];
                 prism_coefs<FORM, P, KIND>(row[c] + (i < C::NI ? i : 0) * (M1 * JQ), w, cf);
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const float x = t < T && (C::REM == 0 || i < C::NI) ? (float)cf[t < T ? t : 0] : 0.0f;
-                    ah[c][t] = (__bf16)x;
-                    al[c][t] = (__bf16)(x - (float)ah[c][t]);
+                for (int t = 0; t < 8; t += 2) {
+                    // two at a time: one conversion instruction
+                    const f2v x = {t < T ? (float)cf[t < T ? t : 0] : 0.0f, t + 1 < T ? (float)cf[t + 1 < T ? t + 1 : 0] : 0.0f};
+                    const bf2v hi = __builtin_convertvector(x, bf2v);
+                    const bf2v lo = __builtin_convertvector(x - __builtin_convertvector(hi, f2v), bf2v);
+                    ah[c][t] = hi[0];
+                    ah[c][t + 1] = hi[1];
+                    al[c][t] = lo[0];
+                    al[c][t + 1] = lo[1];
                 }
             }
 #pragma unroll
