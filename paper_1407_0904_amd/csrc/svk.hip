@@ -1459,7 +1459,15 @@ hipError_t launch_svk(int form, int precision, const dev::SvkArgs& a, hipStream_
     if (reverse) {
         if (form == COFFEE_SVK_RESIDUAL)
             hipLaunchKernelGGL((dev::k_svk_res_adj<D, P, NQ>), dim3(grid), dim3(256), 0, s, a);
-        else if (a.grad_u || a.det_u)
+        else if (!a.grad_u && !a.grad_coords && !a.det_x) {
+            // the values alone: the energy's own kernel, without tables, and at
+            // the occupancy that a gather wants (600,011 cells, mesh / random
+            // order, us, the coordinates' kernel -> this: P1 tetrahedra 19 / 40 ->
+            // 14 / 40, P2 71 / 113 -> 40 / 100, P2 triangles 21 / 57 -> 15 / 56)
+            dev::SvkArgs v = a;
+            v.out = a.cell_value;
+            if (v.out) hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 0, double>), dim3(grid), dim3(256), 0, s, v);
+        } else if (a.grad_u || a.det_u)
             hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 3, double>), dim3(rgrid(3)), dim3(256), 0, s, a);
         else
             hipLaunchKernelGGL((dev::k_svk_vec<D, P, NQ, 2, double>), dim3(rgrid(2)), dim3(256), 0, s, a);

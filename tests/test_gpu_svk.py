@@ -392,3 +392,29 @@ def test_svk_residual_adjoint_without_displacement_gradient(cf, d, p, cellmajor)
     torch.cuda.synchronize()
     assert torch.equal(cv[0], cv[1]) and torch.equal(cv[0], cv[2])
     assert float((full - only).abs().max()) <= 1e-12 * float(full.abs().max())
+
+
+@pytest.mark.parametrize("cellmajor", [True, False])
+@pytest.mark.parametrize("d,p", [(3, 1), (3, 2), (2, 1), (2, 2)])
+def test_svk_energy_values_alone(cf, oracle, d, p, cellmajor):
+    """The energy's reverse pass without any gradient array runs the forward kernel: its values against the oracle, at
+    counts around a wave and a workgroup; nothing beyond them is written, and no values at all is a call that succeeds."""
+    import torch
+    from gpu_util import TOL, cell_rel_err, to_dev
+    rng = np.random.default_rng(510 + 10 * d + p)
+    mesh = I.make_mesh(d, 17 if d == 2 else 5, 0.1, rng)
+    u = _disp(mesh, p, rng)
+    cst = [1.3, 0.7]
+    ref = oracle.assemble("svk_energy", mesh, p, fields=[u], constants=cst).reshape(-1, 1)
+    coords, c2v, _ = to_dev(mesh, [])
+    dev = coords.device
+    vals, dofs = torch.as_tensor(u.values, device=dev), torch.as_tensor(u.cell_to_dof, device=dev)
+    for count in (1, 63, 64, 65, 257, 514):
+        m = dofs[:count].contiguous()
+        f = cf.DeviceField(vals[m.long()].contiguous() if cellmajor else vals, None if cellmajor else m, p, d)
+        cv = torch.full((count + 1,), -7.0, dtype=torch.float64, device=dev)
+        args = ("svk_energy", d, p, coords, c2v[:count].contiguous())
+        cf.coffee_assemble_adjoint(*args, coeffs=[f], constants=cst, cell_value=cv[:count], grads=False)
+        cf.coffee_assemble_adjoint(*args, coeffs=[f], constants=cst, grads=False)
+        got = cv.cpu().numpy()
+        assert cell_rel_err(got[:count].reshape(-1, 1), ref[:count]) < TOL["fp64"] and got[count] == -7.0
