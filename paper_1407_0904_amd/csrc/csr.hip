@@ -409,21 +409,28 @@ void scatter_runs(const T* A, const int32_t* map, int64_t ncells, const int64_t*
                        dim3(dev::kCsrThreads), 0, s, A, map, ncells, row_ptr, col_idx, values);
 }
 
-// Runs of SAFE cells, which fit the LDS matrix in any order of the cells, where
-// all of them are resident at once (two workgroups per CU): such a mesh has too
-// few long runs for the CUs, and a long run of scattered cells is taken in
-// parts, one after the other. Helmholtz P1 tetrahedra FP64, the whole call in
-// a graph, long runs / SAFE, us: cells in mesh order 1,293 10.0 / 9.0, 10,365
-// (471 runs) 10.8 / 10.3, 24,573 (1,117 runs) 12.6 / 15.7; in random order
-// 1,293 21.6 / 10.1, 10,365 24.7 / 13.5, 24,573 28.2 / 22.5.
+// The shortest runs that are all resident at once (two workgroups per CU), of
+// SAFE cells, which fit the LDS matrix in any order of the cells, of half the
+// long runs' cells, and else of CELLS: a small mesh has too few long runs for
+// the CUs, and a long run of scattered cells is taken in parts, one after the
+// other. Mass matrices FP64, the whole call in a graph, runs of SAFE / half /
+// CELLS, us: P1 tetrahedra in mesh order 1,293 cells (Helmholtz) 9.0 / - /
+// 10.0, 12,001 13.3 / 11.9 / 12.4, 20,007 15.0 / 13.0 / 13.6, in random order 10.1 / - / 21.6, 17.7 / 19.4 / 26.8, 21.0 / 22.0 / 28.8 (one thread per tensor row 20.8
+// for 12,001 and 28.0 for 20,007); P1 triangles 20,007 13.0 / 11.6 / 12.0 and
+// 16.4 / 16.5 / 19.0 (17.6). Beyond, in random order, P1 triangles are near
+// one thread per tensor row: 24,003 cells 20.9 (19.9), 50,003 31.5 (30.2).
 template <typename T, int NL, int NC, int CELLS>
 bool scatter_launch(const T* A, const int32_t* map, int64_t ncells, const int64_t* row_ptr, const int32_t* col_idx,
                     T* values, hipStream_t s) {
     constexpr int SAFE = dev::csr_safe(NL, NC, CELLS);
+    constexpr int MID = CELLS / 2 > SAFE ? CELLS / 2 : SAFE;
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return false;
-    if (ncells <= (int64_t)SAFE * 2 * num_cu(device))
+    const int64_t resident = 2 * num_cu(device);  // workgroups
+    if (ncells <= SAFE * resident)
         scatter_runs<T, NL, NC, SAFE>(A, map, ncells, row_ptr, col_idx, values, s);
+    else if (MID > SAFE && ncells <= MID * resident)
+        scatter_runs<T, NL, NC, MID>(A, map, ncells, row_ptr, col_idx, values, s);
     else
         scatter_runs<T, NL, NC, CELLS>(A, map, ncells, row_ptr, col_idx, values, s);
     return true;

@@ -247,3 +247,48 @@ def test_csr_long_and_short_runs(cf, oracle, form, cell, p, shuffled, prec):
         np.add.at(ref, at, A[:count].ravel())
         # entries are sums of at most a few dozen tensor values of that size
         assert np.abs(got - ref).max() <= 10 * TOL[prec] * np.abs(A).max(), count
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("shuffled", [False, True])
+@pytest.mark.parametrize("form,cell,p,half", [
+    ("mass", "triangle", 1, 43), ("mass", "triangle", 3, 7), ("elasticity", "triangle", 1, 21),
+    ("mass", "tetrahedron", 1, 57), ("mass", "tetrahedron", 2, 10), ("elasticity", "tetrahedron", 1, 15),
+    ("mass", "prism", 1, 14), ("mass", "prism", 2, 4)])
+def test_csr_runs_of_half_length(cf, oracle, form, cell, p, half, prec, shuffled):
+    """Meshes between those of the shortest and of the longest runs: the largest count whose runs of half the cells are
+    all resident (two workgroups per CU) and one cell more; the matrix against the sum of the oracle's tensors."""
+    import torch
+    from gpu_util import TOL, to_dev
+    d = 2 if cell == "triangle" else 3
+    nc = d if form == "elasticity" else 1
+    nl = {"triangle": (p + 1) * (p + 2) // 2, "tetrahedron": (p + 1) * (p + 2) * (p + 3) // 6,
+          "prism": (p + 1) * (p + 2) // 2 * (p + 1)}[cell]
+    most = half * 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(900 + 10 * d + p)
+    n = int(np.ceil(((most + 1) / {"triangle": 2, "tetrahedron": 6, "prism": 2}[cell]) ** (1 / d)))
+    mesh = I.make_prism_mesh(n, 0.1, rng) if cell == "prism" else I.make_mesh(d, n, 0.1, rng)
+    if p == 1:
+        c2d, nd = mesh.cells, mesh.nvert
+    else:  # distinct dofs per cell, shared by neighbours in number: any map is a valid space for the scatter
+        nd = mesh.ncells * nl // 5 + 2 * nl
+        c2d = (np.arange(mesh.ncells)[:, None] * (nl // 5 + 1) + np.arange(nl)[None, :]) % nd
+    order = rng.permutation(mesh.ncells) if shuffled else np.arange(mesh.ncells)
+    cells = np.ascontiguousarray(mesh.cells[order][:most + 1])
+    c2d = np.ascontiguousarray(np.asarray(c2d, dtype=np.int32)[order][:most + 1])
+    cst = [1.5, 0.5] if form == "elasticity" else []
+    coords, c2v, _ = to_dev(I.Mesh(d, n, mesh.coords, cells), [])
+    code = {"triangle": 2, "tetrahedron": 3, "prism": 6}[cell]
+    dofs = torch.as_tensor(c2d, device=coords.device)
+    row_ptr, col_idx = cf.coffee_csr_pattern(dofs, nd, nc)
+    rp, ci = row_ptr.cpu().numpy(), col_idx.cpu().numpy()
+    A = oracle.assemble(form, I.Mesh(d, n, mesh.coords, cells), p, constants=cst)
+    keys = np.repeat(np.arange(nd * nc), np.diff(rp)) * (nd * nc) + ci
+    g = np.concatenate([c2d.astype(np.int64) * nc + c for c in range(nc)], axis=1)
+    at = np.searchsorted(keys, (g[:, :, None] * (nd * nc) + g[:, None, :]).ravel()).reshape(len(g), -1)
+    for count in (most, most + 1):
+        got = cf.coffee_assemble_csr(form, code, p, coords, c2v[:count].contiguous(), row_ptr, col_idx, nd,
+                                     cell_to_dof=dofs[:count].contiguous(), constants=cst, precision=prec).cpu().numpy()
+        ref = np.bincount(at[:count].ravel(), weights=A[:count].reshape(count, -1).ravel(), minlength=len(ci))
+        # entries share a cell's largest entry as their scale; sums of up to a few dozen of them per nonzero
+        assert np.abs(got - ref).max() <= 4 * TOL[prec] * np.abs(ref).max()
