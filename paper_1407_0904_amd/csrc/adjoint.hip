@@ -256,6 +256,9 @@ __global__ __launch_bounds__(256) void k_adjoint_linear(AdjArgs A) {
 // grid (one workgroup per CU and residency) now has all loads of the next
 // cells in flight over the combining, complete before the flush issues its
 // atomics: 170 -> 128 us (eight workgroups per CU 153); P2 triangles 49 -> 34.
+// Values alone and the deterministic mode take the same grid: 600,011 P2
+// tetrahedra, against the contraction with R at eight workgroups per CU, 586 ->
+// 99 us and, with the sort, 1,379 -> 886.
 
 // The H of P2 tetrahedra (144 registers) and what is formed from them need one
 // wave per SIMD: at two, 255 registers spilled (352 us against 190).

@@ -413,12 +413,14 @@ void scatter_runs(const T* A, const int32_t* map, int64_t ncells, const int64_t*
 // SAFE cells, which fit the LDS matrix in any order of the cells, of half the
 // long runs' cells, and else of CELLS: a small mesh has too few long runs for
 // the CUs, and a long run of scattered cells is taken in parts, one after the
-// other. Mass matrices FP64, the whole call in a graph, runs of SAFE / half /
-// CELLS, us: P1 tetrahedra in mesh order 1,293 cells (Helmholtz) 9.0 / - /
-// 10.0, 12,001 13.3 / 11.9 / 12.4, 20,007 15.0 / 13.0 / 13.6, in random order 10.1 / - / 21.6, 17.7 / 19.4 / 26.8, 21.0 / 22.0 / 28.8 (one thread per tensor row 20.8
-// for 12,001 and 28.0 for 20,007); P1 triangles 20,007 13.0 / 11.6 / 12.0 and
-// 16.4 / 16.5 / 19.0 (17.6). Beyond, in random order, P1 triangles are near
-// one thread per tensor row: 24,003 cells 20.9 (19.9), 50,003 31.5 (30.2).
+// other. Mass matrices FP64, the whole call in a graph, us, runs of SAFE / half
+// / CELLS (one thread per tensor row): P1 tetrahedra in mesh order, 12,001
+// cells, 13.3 / 11.9 / 12.4 (17.1), 20,007 15.0 / 13.0 / 13.6 (22.8); in random
+// order 17.7 / 19.4 / 26.8 (20.8) and 21.0 / 22.0 / 28.8 (28.0); Helmholtz,
+// 1,293 cells, SAFE / CELLS 9.0 / 10.0 and 10.1 / 21.6 (13.0); P1 triangles,
+// 20,007, 13.0 / 11.6 / 12.0 (14.1) and 16.4 / 16.5 / 19.0 (17.6). Beyond, P1
+// triangles in random order are near one thread per tensor row: 24,003 cells
+// 20.9 (19.9), 50,003 31.5 (30.2).
 template <typename T, int NL, int NC, int CELLS>
 bool scatter_launch(const T* A, const int32_t* map, int64_t ncells, const int64_t* row_ptr, const int32_t* col_idx,
                     T* values, hipStream_t s) {

@@ -438,7 +438,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 //   diffusion       FP32         376              301          299
 //   diffusion       BF16X3       258              269          254
 // (the BF16X3 mass form also packs its products: kMassParts). 65,536 P3
-// prisms: diffusion FP64 765 -> 367, FP32 415 -> 217, BF16X3 222 -> 175; mass
+// prisms: diffusion FP64 765 -> 367, FP32 415 -> 217, BF16X3 222 -> 157; mass
 // BF16X3 109 -> 128 with one product per slot, 101 packed.
 
 // Workgroup barrier that orders LDS accesses only. Nothing passes between the

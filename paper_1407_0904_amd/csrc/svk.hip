@@ -1448,7 +1448,10 @@ hipError_t launch_svk(int form, int precision, const dev::SvkArgs& a, hipStream_
     // gradients, us: P2 tetrahedra, 196,608 / 2,058,000 cells: one per CU 54 and
     // 495, two 58 and 494, eight 63 and 519; P1 tetrahedra, 196,608 /
     // 1,296,000: two 18 and 93, three 19 and 108, eight 20 and 96; P1
-    // triangles, 720,000: one 37, two 29, three 25, eight 27). Loading each
+    // triangles, 720,000: one 37, two 29, three 25, eight 27; the coordinates
+    // alone, against eight per CU and no loads ahead, P2 tetrahedra, 200,003, 45 ->
+    // 35, P1 tetrahedra, 600,011, 61 -> 31; the deterministic mode, whose sort
+    // outweighs the kernel, 486 -> 459 and 564 -> 563). Loading each
     // cell's values behind the previous one's atomics, eight per CU: P2
     // tetrahedra 59 and 557, P1 22 and 95, P1 triangles 29, P2 triangles,
     // 180,000, 21 -> 18.
