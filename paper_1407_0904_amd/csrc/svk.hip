@@ -205,9 +205,6 @@ __device__ inline void svk_load(const SvkArgs& A, int64_t cell, Geom<D>& g, doub
 
 typedef unsigned int svk_u32x4 __attribute__((ext_vector_type(4)));
 
-template <int D, int P>
-constexpr int svk_tab_elems(int nq) { return nq + D * nq * nsc(D, P); }
-
 // The per-cell results of a reverse pass: the vertex-coordinate gradients vx
 // (seed already applied) and, if U, the displacement-dof gradients
 // f * g[c * NS + r] (component-blocked). Deterministic mode writes them to
